@@ -113,7 +113,7 @@ void fill_geometry(const bf_bank_desc* d, GridDev* g, BankDev* b) {
   b->precision = d->precision;
   b->fft_m = 0;
   if (d->precision == BF_FFT) {
-    // real FFT length N = 2M = 8192 for every L (<= 4096): its kernel (k_fft4k) runs at 1.5
+    // real FFT length N = 2M = 8192 for every L (<= 4096): its kernel (k_fft4k_search) runs at 1.5
     // to 2.6 times the flop rate of the general one (k_fft_main at N = 4096 and 2048), which
     // outweighs the up to 8% less transform work per valid output, M log2 M / (2M - L + 1),
     // that a shorter transform has for short templates.  BF_FFT_POINTS = 1024, 2048 or 4096

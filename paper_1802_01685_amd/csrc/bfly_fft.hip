@@ -80,21 +80,6 @@ __device__ __forceinline__ float2 twiddle16(float2 b) {
   }
 }
 
-// twiddle16 for a q that is a constant after unrolling.
-template <bool INV>
-__device__ __forceinline__ float2 twiddle16_q(float2 b, int q) {
-  switch (q) {
-    case 0: return twiddle16<0, INV>(b);
-    case 1: return twiddle16<1, INV>(b);
-    case 2: return twiddle16<2, INV>(b);
-    case 3: return twiddle16<3, INV>(b);
-    case 4: return twiddle16<4, INV>(b);
-    case 5: return twiddle16<5, INV>(b);
-    case 6: return twiddle16<6, INV>(b);
-    default: return twiddle16<7, INV>(b);
-  }
-}
-
 // One radix-2 stage of span S (s in the DIT recursion) over t[], groups of S from offset G.
 template <int R, int S, int G, int K, bool INV>
 __device__ __forceinline__ void dft_bfly(float2 (&t)[R]) {
@@ -766,9 +751,10 @@ __global__ __launch_bounds__(Plan<M>::T, OCC) void k_fft_main(const BatchHdr* __
 }
 
 // ---------------------------------------------------------------------------------------
-// The search kernel at M = 4096 (real FFTs of N = 8192 points; the length the planner picks
-// for templates of roughly 1,500 to 4,096 taps).  One transform per work-group of 256
-// threads (one wave per SIMD), 16 points per thread, two work-groups per CU:
+// The sigma, tails and single-pass kernel at M = 4096 (real FFTs of N = 8192 points).  The
+// plain search is k_fft4k_search below, the same transform on more threads; here the wave sums
+// of rho^2 fix which outputs a thread holds.  One transform per work-group of 256 threads (one
+// wave per SIMD), 16 points per thread, two work-groups per CU:
 // * The thread owns inverse-FFT butterflies j0 = t and j1 = 512 - t of the first radix-8
 //   pass, whose points j + 512 r are closed under the mirror p -> M - p of the real-FFT
 //   post-processing.  It keeps the data spectrum X_b at those points in registers for the
@@ -801,6 +787,7 @@ constexpr int PADN = M + M / 8;   // the largest stage layout (SH = 3)
 // (3, 3, 0) 235, (3, 3, 3) 233-235.
 constexpr int S1 = 5, S2 = 3, S3 = 0;
 constexpr unsigned ROW_BYTES = (M + 2) * 8;   // one spectrum row (bins 0..M, padded)
+constexpr int SPECIAL_WAVE = 0;   // k_fft4k_search: the wave of butterflies 0 and 256
 }  // namespace fft4k
 
 // A buffer resource on one spectrum row: the loads below address it with a 32-bit per-lane
@@ -946,15 +933,9 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
 
   // first-pass butterflies j0 = t and j1 = 512 - t (thread 0: 0, and 256 handed over);
   // pair r = (a_r, M - a_r) with a_r = t + 512 r; its post-processing twiddle
-  // LEAN forms the pair twiddles and pass 4's twiddle powers per template instead of keeping
-  // them in registers (for builds short of registers; off in every mode compiled now).
-  constexpr bool LEAN = false;
-  const float2 wt = cis_rev<true>((float)t / (float)(2 * M));   // wpair[r] = wt exp(2 pi i r/16)
-  float2 wpair[LEAN ? 1 : 8];
-  if constexpr (!LEAN) {
+  float2 wpair[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) wpair[r] = cis_rev<true>((float)(t + 512 * r) / (float)(2 * M));
-  }
+  for (int r = 0; r < 8; ++r) wpair[r] = cis_rev<true>((float)(t + 512 * r) / (float)(2 * M));
   // lanes 0..3 of wave 0: pair (256 + 512 t, M - 256 - 512 t) of butterfly 256
   const bool helper = t < 4;
   const int ha_idx = 256 + 512 * (t & 3);
@@ -970,16 +951,11 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
       tab2[i] = cis_rev<true>((float)((m2 * r2) & 63) / 64.0f);
     }
   }
-  float2 tw4a[LEAN ? 1 : 7], tw4b[LEAN ? 1 : 7];
-  if constexpr (LEAN) {
-    tw4a[0] = cis_rev<true>((float)t / 4096.0f);
-    tw4b[0] = cis_rev<true>((float)(t + 256) / 4096.0f);
-  } else {
+  float2 tw4a[7], tw4b[7];
 #pragma unroll
-    for (int r = 1; r < 8; ++r) {
-      tw4a[r - 1] = cis_rev<true>((float)((t * r) & 4095) / 4096.0f);
-      tw4b[r - 1] = cis_rev<true>((float)(((t + 256) * r) & 4095) / 4096.0f);
-    }
+  for (int r = 1; r < 8; ++r) {
+    tw4a[r - 1] = cis_rev<true>((float)((t * r) & 4095) / 4096.0f);
+    tw4b[r - 1] = cis_rev<true>((float)(((t + 256) * r) & 4095) / 4096.0f);
   }
   __syncthreads();
 
@@ -1040,27 +1016,19 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
     const int pos_end = (int)min((int64_t)valid, sg.W - (int64_t)tau_base);
     // The single pass keeps the bin's argmax as 1 + (k - the bin's first template), two
     // outputs to a register (0: none yet), to stay within 256 registers with sinv below.
-    constexpr bool PACK = MODE == MODE_ONEPASS;
     float binmax[NO];
-    int binarg[PACK ? 1 : NO];
-    unsigned barg2[PACK ? (NO + 1) / 2 : 1];
+    unsigned barg2[SMAX];
     // sigma, tails and single-pass modes: scale / sqrt(E) with 1/sqrt(E) rounded to float
     // (0 if invalid); scale is a power of two, so y sinv = (y scale) (1/sqrt(E))_f32 exactly
     float sinv[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o) {
-      if constexpr (MODE == MODE_SEARCH || MODE == MODE_ONEPASS) {
+      if constexpr (MODE == MODE_ONEPASS) {
         binmax[o] = -1.0f;
-        if constexpr (PACK) {
-          if ((o & 1) == 0) barg2[o >> 1] = 0u;
-        } else {
-          binarg[o] = -1;
-        }
+        if ((o & 1) == 0) barg2[o >> 1] = 0u;
       }
-      if constexpr (MODE != MODE_SEARCH) {
-        const int pos = 2 * t + 512 * (o >> 1) + (o & 1);
-        sinv[o] = pos < pos_end ? scale * (float)sg.inv_norm[tau_base + pos] : 0.0f;
-      }
+      const int pos = 2 * t + 512 * (o >> 1) + (o & 1);
+      sinv[o] = pos < pos_end ? scale * (float)sg.inv_norm[tau_base + pos] : 0.0f;
     }
     const int k_lo = b_lo * nfd, k_hi = b_hi * nfd;
     float2 ha[8], hb[8], hha = make_float2(0.0f, 0.0f), hhb = hha;
@@ -1105,8 +1073,7 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
       float2 v0[8], v1[8];
 #pragma unroll
       for (int r = 0; r < 8; ++r)
-        mirror_pair(ha[r], xa[r], hb[r], xb[r],
-                    LEAN ? twiddle16_q<true>(wt, r) : wpair[LEAN ? 0 : r], v0[r], v1[7 - r]);
+        mirror_pair(ha[r], xa[r], hb[r], xb[r], wpair[r], v0[r], v1[7 - r]);
       if (helper) {
         // the helpers are lanes 0..3 of wave 0, so t is their lane index
         const int h = lane_here();
@@ -1150,20 +1117,7 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
         pass8x2<64, false, S2, S3>(bufq, bufp, w, w, y0, y1);
       }
       __syncthreads();
-      if constexpr (LEAN) {
-        // pass 4's twiddle powers as running products of the bases
-        float2 wa[7], wb[7];
-        wa[0] = tw4a[0];
-        wb[0] = tw4b[0];
-#pragma unroll
-        for (int r = 1; r < 7; ++r) {
-          wa[r] = cmul(wa[r - 1], tw4a[0]);
-          wb[r] = cmul(wb[r - 1], tw4b[0]);
-        }
-        pass8x2<512, true, S3, 0>(bufp, bufq, wa, wb, y0, y1);
-      } else {
-        pass8x2<512, true, S3, 0>(bufp, bufq, tw4a, tw4b, y0, y1);
-      }
+      pass8x2<512, true, S3, 0>(bufp, bufq, tw4a, tw4b, y0, y1);
       // output slot o = 2 s + part: s even -> y0[s / 2], s odd -> y1[s / 2]
       auto outv = [&](int o) -> float {
         const int s = o >> 1;
@@ -1182,8 +1136,9 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
           q = fmaf(rr, rr, q);
           if constexpr (MODE == MODE_ONEPASS) {
             mr = fmaxf(mr, fabsf(rr));
-            // the running maximum of the search (below), in the same sweep; the low (even o)
-            // or high (odd o) half of the register takes rel1 where |v| is a new maximum
+            // the bin's running maximum in the same sweep, lowest k on ties (k increases,
+            // strict >); the low (even o) or high (odd o) half of the register takes rel1
+            // where |v| is a new maximum
             const unsigned rel1 = (unsigned)(k - bin * nfd + 1);
             if (o & 1)
               max_arg16<1>(v, binmax[o], barg2[o >> 1], rel1);
@@ -1225,29 +1180,14 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
         }
         continue;
       }
-      // running maximum over the bin's templates, lowest k on ties (k increases, strict >)
-      if constexpr (MODE == MODE_SEARCH) {
-#pragma unroll
-        for (int o = 0; o < NO; ++o) {
-          const float a = fabsf(outv(o));
-          const bool g = a > binmax[o];
-          binarg[o] = g ? k : binarg[o];
-          binmax[o] = g ? a : binmax[o];
-        }
-      }
       if (--left == 0) {
         // end of bin: spectrogram row, spectrum sum, packed per-offset maxima
         unsigned long long fix = 0ull;
 #pragma unroll
         for (int o = 0; o < NO; ++o) {
           const int pos = 2 * t + 512 * (o >> 1) + (o & 1);
-          int ba;
-          if constexpr (PACK) {
-            const unsigned r1 = (barg2[o >> 1] >> (16 * (o & 1))) & 0xFFFFu;
-            ba = r1 ? bin * nfd + (int)r1 - 1 : -1;
-          } else {
-            ba = binarg[o];
-          }
+          const unsigned r1 = (barg2[o >> 1] >> (16 * (o & 1))) & 0xFFFFu;
+          const int ba = r1 ? bin * nfd + (int)r1 - 1 : -1;
           if (pos < pos_end && ba >= 0) {
             const int tau = tau_base + pos;
             const float v = binmax[o] * scale;
@@ -1269,17 +1209,343 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
                       ((unsigned long long)__float_as_uint(v) << 32) | (0xFFFFFFFFull - kg));
           }
           binmax[o] = -1.0f;
-          if constexpr (PACK) {
-            if (o & 1) barg2[o >> 1] = 0u;   // after both outputs of the register
-          } else {
-            binarg[o] = -1;
-          }
+          if (o & 1) barg2[o >> 1] = 0u;   // after both outputs of the register
         }
         fix = wave_sum_u64(fix);
         if ((t & 63) == 0 && fix != 0ull) atomicAdd(sg.spec_acc + bin, fix);
         ++bin;
         left = nfd;
       }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// The plain search at M = 4096: the transform of k_fft4k, operation for operation (the same
+// values bit for bit), with 512 threads and 8 points per thread, so that two work-groups put
+// four waves on a SIMD.  Bound by VALU issue: 720,000 templates of L = 2000 against 2 x 126,001
+// offsets take 177 ms (227 ms with 256 threads of 16 points, two waves per SIMD: issue 77%
+// there, 97% here), 65,536 of L = 4096 against 126,977 offsets 13.0 ms (15.8 ms).
+// * First pass: lanes 2i and 2i + 1 own the radix-8 butterflies i and 512 - i, each other's
+//   mirror under p -> M - p.  Each lane forms C = conj(H) X at its own 8 points and the four
+//   pairs whose lower-numbered slot (0..3) is its own; the partner's C and the partner's half
+//   of each pair come through DPP operands of the additions (quad_perm [1, 0, 3, 2]), which
+//   cost no instruction.  Seen from the upper point the pair's twiddle is minus its conjugate,
+//   and the results only change sign twice.  Butterflies 0 and 256 are their own mirrors:
+//   lanes 0 and 1 of wave 0 hold a lower half of one and an upper half of the other each.
+// * The template's spectrum is loaded after the third pass, when the twiddles and the points
+//   of passes 2 and 3 no longer need the registers (loading it in the first pass spilled 17
+//   values per template); a third of a template's time covers the L2.
+// * Pass 2 runs butterfly (wave + 8 lane), whose twiddles depend on the wave only: scalar
+//   registers, no table reads (with pass 3's and without this: LDS active 61% of the time and
+//   204 ms), and none for wave 0, whose twiddles are 1 (it has the two self-mirrored butterflies
+//   instead).  Passes 3 and 4 run butterfly t.
+// * The template loop is unrolled by the two LDS buffers' parity, so their addresses are
+//   immediates; each bin starts on parity 0 behind one more barrier.
+// * The last pass leaves the thread points t + 512 r, outputs 2t + 1024 r + part; only the
+//   first RMAX levels r can hold valid offsets, the last of them often in few waves.  The
+//   running maxima are merged as in k_fft4k at each bin's end.
+// ---------------------------------------------------------------------------------------
+
+template <int V>
+struct IntC {
+  static constexpr int value = V;
+};
+
+// The partner lane's value (lanes 2i and 2i + 1 exchange).
+__device__ __forceinline__ float swap1(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float2 swap1(float2 v) { return make_float2(swap1(v.x), swap1(v.y)); }
+
+__device__ __forceinline__ float2 row_load2(__amdgpu_buffer_rsrc_t r, unsigned voff,
+                                            unsigned soff) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+  return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+}
+
+// Running maximum of |a + b| (SUB: |a - b|) with the template reaching it, in one 64-bit word:
+// the float's bits above nk = ~k (local template k).  Non-negative floats, and with them these
+// words read as doubles, order as their bits, so one v_max_f64 (at the rate of a 32-bit
+// operation; denormals are kept) takes the larger magnitude and on ties the lower k, where a
+// compare and two selects took three.  The sum, the last butterfly's output, is written straight into
+// the high half of a fixed register pair whose low half holds nk for the whole template.  It
+// is finite: samples are below 1e30 and the transform adds less than 1e6 to that.
+template <bool SUB>
+__device__ __forceinline__ void max_key(double& best, float a, float b, unsigned nk) {
+  if constexpr (SUB)
+    asm("v_sub_f32 v127, %1, %2\n\tv_max_f64 %0, %0, |v[126:127]|"
+        : "+v"(best) : "v"(a), "v"(b), "{v126}"(nk) : "v127");
+  else
+    asm("v_add_f32 v127, %1, %2\n\tv_max_f64 %0, %0, |v[126:127]|"
+        : "+v"(best) : "v"(a), "v"(b), "{v126}"(nk) : "v127");
+}
+
+// The eight points of one butterfly of a radix-8 Stockham pass, R1 slots apart from rd,
+// twiddled by w[r - 1] (not where `twiddle` is false: all are 1).
+template <int R1>
+__device__ __forceinline__ void read8(const float2* rd, const float2 (&w)[7], float2 (&y)[8],
+                                      bool twiddle = true) {
+#pragma unroll
+  for (int r = 0; r < 8; ++r) y[r] = rd[R1 * r];
+  if (twiddle) {
+#pragma unroll
+    for (int r = 1; r < 8; ++r) y[r] = cmul(y[r], w[r - 1]);
+  }
+}
+
+template <int RMAX>
+__global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restrict__ hdr,
+                                                         BankDev b, SearchDev p) {
+  using namespace fft4k;
+  static_assert(RMAX >= 5 && RMAX <= 8, "output levels: L <= 4096 leaves more than 4096 offsets");
+  constexpr int NO = 2 * RMAX;          // real outputs per thread that can be valid
+  // stage layouts (element i at i + (i >> SH)): SH = 5 after the first pass, 6 after the
+  // second, none after the third; every read and write below but the first pass's writes is
+  // free of bank conflicts over each half wave
+  constexpr int BUF = M + M / 32;
+  __shared__ float2 lds[2 * BUF];
+  __shared__ float2 tab3[7 * 64];
+  const SegDesc* segs = hdr_segs(hdr);
+  const float2* spectra = (const float2*)b.data;
+  const int n_ranges = hdr->n_ranges;
+  const int64_t n_items = hdr->n_items;
+  const int valid = 2 * M - b.L + 1;
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const float scale = 0.5f / (float)M;
+  const int nfd = b.n_fdot;
+
+  // first-pass thread t1: lanes 2i and 2i + 1 own butterflies i and 512 - i (i = 0: 0 and 256)
+  const int t1 = (t + 512 - 64 * SPECIAL_WAVE) & 511;
+  const int i1 = t1 >> 1, odd = t1 & 1;
+  const int j = odd ? (i1 ? 512 - i1 : 256) : i1;
+  // slots 0..3 at point j + 512 s, slots 4..7 at jh + 512 s
+  const int jh = t1 == 0 ? 256 : t1 == 1 ? 512 : j;
+  const unsigned va = 8u * (unsigned)j, vb = 8u * (unsigned)jh;
+  float2 w[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    // the pair's twiddle exp(2 pi i a / N) from its lower point a = i + 512 r; the upper
+    // point's is minus its conjugate
+    if (t1 == 1 || !odd) {
+      w[s] = cis_rev<true>((float)(j + 512 * s) / (float)(2 * M));
+    } else {
+      const float2 q = cis_rev<true>((float)(i1 + 512 * (7 - s)) / (float)(2 * M));
+      w[s] = make_float2(-q.x, q.y);
+    }
+  }
+  // twiddle powers: pass 2 runs butterfly wave + 8 lane, so its twiddles are the wave's
+  // (scalar registers); passes 3 and 4 run butterfly t
+  float2 tw2[7], tw4[7];
+#pragma unroll
+  for (int r = 1; r < 8; ++r) {
+    const float2 q = cis_rev<true>((float)((wave * r) & 63) / 64.0f);
+    tw2[r - 1].x = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(q.x)));
+    tw2[r - 1].y = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(q.y)));
+    tw4[r - 1] = cis_rev<true>((float)((t * r) & 4095) / 4096.0f);
+  }
+  if (t < 7 * 64) tab3[t] = cis_rev<true>((float)((t % 64 * (t / 64 + 1)) & 511) / 512.0f);
+  const int w1 = padk<5>(8 * j);                 // pass 1 writes 8 consecutive points
+  const int r2 = 8 * lane + (lane >> 2) + wave;  // pass 2 reads wave + 8 lane + 512 r
+  const int w2 = 65 * lane + wave;               // and writes 64 lane + wave + 8 r
+  const int r3 = t + wave;                       // pass 3 reads t + 512 r
+  const int w3 = 512 * wave + lane;              // and writes 512 wave + lane + 64 r
+
+  const int64_t total_tiles = hdr->total_tiles;
+  for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+    int rg;
+    int64_t tt;
+    if (n_ranges % 8 == 0) {
+      const int64_t q = item / 8;
+      rg = (int)(item % 8) + 8 * (int)(q / total_tiles);
+      tt = q % total_tiles;
+    } else {
+      rg = (int)(item % n_ranges);
+      tt = item / n_ranges;
+    }
+    int lo = 0, hi = hdr->n_segs - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (segs[mid].tile0 <= tt) lo = mid; else hi = mid - 1;
+    }
+    const SegDesc& sg = segs[lo];
+    const int64_t blk = tt - sg.tile0;
+    const int tau_base = (int)(blk * valid);     // series are shorter than 2^31 samples
+    const int b_lo = (int)((int64_t)rg * b.n_bins / n_ranges);
+    const int b_hi = (int)((int64_t)(rg + 1) * b.n_bins / n_ranges);
+    const float2* xsrc = sg.xspec + blk * (int64_t)(M + 2);
+    float2 x[8];
+    {
+      const __amdgpu_buffer_rsrc_t xr = row_rsrc(xsrc);
+#pragma unroll
+      for (int s = 0; s < 8; ++s) x[s] = row_load2(xr, s < 4 ? va : vb, 4096u * s);
+    }
+    const float2 x2 = xsrc[M / 2];   // uniform
+    // output o = 2 r + part sits at block position 2t + 1024 r + part; it is a valid offset
+    // of the series below this bound
+    const int pos_end = (int)min((int64_t)valid, sg.W - (int64_t)tau_base);
+    // levels r with an output of this wave below `valid`
+    const bool last = 128 * wave + 1024 * (RMAX - 1) < valid;
+    double best[NO];
+#pragma unroll
+    for (int o = 0; o < NO; ++o) best[o] = 0.0;
+    const int k_lo = b_lo * nfd, k_hi = b_hi * nfd;
+    float2 h[8], h2;
+    auto load_h = [&](int k) {
+      const __amdgpu_buffer_rsrc_t hr = row_rsrc(spectra + (int64_t)k * (M + 2));
+#pragma unroll
+      for (int s = 0; s < 8; ++s) h[s] = row_load2(hr, s < 4 ? va : vb, 4096u * s);
+      h2 = row_load2(hr, 8u * (M / 2), 0u);
+    };
+    load_h(k_lo);
+    // One template on the buffer pair of parity P: pass 1 writes bufp, pass 2 reads it and
+    // writes bufq, pass 3 writes bufp back, pass 4 reads it; the next template swaps the two,
+    // so three barriers suffice.
+    auto step = [&](auto parity, int k) {
+      constexpr int P = decltype(parity)::value;
+      float2* const bufp = lds + P * BUF;
+      float2* const bufq = lds + (1 - P) * BUF;
+      // ---- spectrum product, post-processing and the first radix-8 pass, in registers
+      float2 v[8];
+      {
+        float2 c[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) c[s] = cmul(cconj(h[s]), x[s]);
+        const float2 c2 = cmul(cconj(h2), x2);
+        float2 ya[4], yb[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const float2 pc = cconj(swap1(c[7 - s]));
+          const float2 e = cadd(c[s], pc);
+          const float2 d = csub(c[s], pc);
+          const float2 o = cmul(d, w[s]);
+          ya[s] = make_float2(e.x - o.y, e.y + o.x);
+          yb[s] = make_float2(e.x + o.y, o.x - e.y);
+        }
+        // the radix-8 DFT's first stage pairs points s and s + 4 (bit-reversed order)
+        auto stage1 = [&](int s, float2 hi) {
+          const int at = bitrev(s, 8);
+          v[at] = cadd(ya[s], hi);
+          v[at + 1] = csub(ya[s], hi);
+        };
+        if (wave == SPECIAL_WAVE) {
+          // lanes 0 and 1 hold both points of their pairs: butterfly 256 in place, butterfly
+          // 0's one slot further down, with its self-mirrored point 2048 (E = 2 Re C, O = 0,
+          // w = i: Y = 2 conj(C)) in slot 4
+          float2 q[5];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            // (the asm keeps this exchange from being shared with the other branch's)
+            asm volatile("" : "+v"(yb[s].x), "+v"(yb[s].y));
+            const float2 o = swap1(yb[s]);
+            q[s].x = t1 < 2 ? yb[s].x : o.x;
+            q[s].y = t1 < 2 ? yb[s].y : o.y;
+          }
+          q[4] = make_float2(c2.x + c2.x, -(c2.y + c2.y));
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            stage1(3 - s, make_float2(t1 == 0 ? q[s + 1].x : q[s].x, t1 == 0 ? q[s + 1].y : q[s].y));
+          // (hides the sums, so that they are not merged with the other branch's: there the
+          // exchange is an operand of the additions and costs no instruction)
+#pragma unroll
+          for (int r = 0; r < 8; ++r) asm volatile("" : "+v"(v[r].x), "+v"(v[r].y));
+        } else {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) stage1(3 - s, swap1(yb[s]));
+        }
+        dft_stages<8, 4, true>(v);
+      }
+#pragma unroll
+      for (int r = 0; r < 8; ++r) bufp[w1 + r] = v[r];
+      __syncthreads();
+      float2 y[8];
+      read8<512 + 16>(bufp + r2, tw2, y, wave != 0);
+      dft<8, true>(y);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) bufq[w2 + 8 * r] = y[r];
+      __syncthreads();
+      {
+        float2 u[7];
+#pragma unroll
+        for (int r = 0; r < 7; ++r) u[r] = tab3[64 * r + lane];
+        read8<512 + 8>(bufq + r3, u, y);
+      }
+      dft<8, true>(y);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) bufp[w3 + 64 * r] = y[r];
+      load_h(min(k + 1, k_hi - 1));   // unconditional (the last one repeats a row)
+      __syncthreads();
+      read8<512>(bufp + t, tw4, y);
+      // the last DFT: two stages, then per output pair r, r + 4 its sum and difference, which
+      // go into the running maxima (lowest k on ties)
+      float2 z[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) z[bitrev(i, 8)] = y[i];
+      dft_stage<8, 2, 0, true>(z);
+      dft_stage<8, 4, 0, true>(z);
+      z[5] = twiddle16<2, true>(z[5]);
+      z[7] = twiddle16<6, true>(z[7]);
+      const unsigned nk = 0xFFFFFFFFu - (unsigned)k;
+      auto keep = [&](auto level) {
+        constexpr int r = decltype(level)::value, q = r & 3;
+        constexpr bool hi = r >= 4;
+        if constexpr (q == 2) {   // times i: z[6] is added as (-z.y, z.x)
+          max_key<!hi>(best[2 * r], z[2].x, z[6].y, nk);
+          max_key<hi>(best[2 * r + 1], z[2].y, z[6].x, nk);
+        } else {
+          max_key<hi>(best[2 * r], z[q].x, z[q + 4].x, nk);
+          max_key<hi>(best[2 * r + 1], z[q].y, z[q + 4].y, nk);
+        }
+      };
+      keep(IntC<0>{});
+      keep(IntC<1>{});
+      keep(IntC<2>{});
+      keep(IntC<3>{});
+      if constexpr (RMAX > 5) keep(IntC<4>{});
+      if constexpr (RMAX > 6) keep(IntC<5>{});
+      if constexpr (RMAX > 7) keep(IntC<6>{});
+      if (last) keep(IntC<RMAX - 1>{});
+    };
+    for (int bin = b_lo; bin < b_hi; ++bin) {
+      const int k_end = (bin + 1) * nfd;
+      for (int k = bin * nfd; k < k_end; k += 2) {
+        step(IntC<0>{}, k);
+        if (k + 1 < k_end) step(IntC<1>{}, k + 1);
+      }
+      __syncthreads();   // the next bin (or item) starts on parity 0 again
+      // end of bin: spectrogram row, spectrum sum, packed per-offset maxima
+      unsigned long long fix = 0ull;
+#pragma unroll
+      for (int o = 0; o < NO; ++o) {
+        const int pos = 2 * t + 1024 * (o >> 1) + (o & 1);
+        const unsigned long long key = __builtin_bit_cast(unsigned long long, best[o]);
+        if (pos < pos_end) {
+          const int tau = tau_base + pos;
+          const float vm = __uint_as_float((unsigned)(key >> 32)) * scale;
+          const double iv = sg.inv_norm[tau];
+          if (iv > 0.0) {
+            const float s = (float)((double)vm * iv);
+            if (sg.spec) {
+              const int row = p.t_block == 1 ? tau : tau / p.t_block;
+              const int64_t at = (int64_t)bin * sg.spec_rows + row;
+              if (p.t_block == 1)
+                sg.spec[at] = s;
+              else
+                atomicMax((unsigned int*)sg.spec + at, __float_as_uint(s));
+            }
+            fix += (unsigned long long)__double2ll_rn((double)s * SPEC_FIX_SCALE);
+          }
+          const unsigned nk = (unsigned)key - (unsigned)b.k_offset;   // ~ the global template
+          atomicMax(sg.mkey + tau, ((unsigned long long)__float_as_uint(vm) << 32) | nk);
+        }
+        best[o] = 0.0;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      fix = wave_sum_u64(fix);
+      if ((t & 63) == 0 && fix != 0ull) atomicAdd(sg.spec_acc + bin, fix);
     }
   }
 }
@@ -1570,6 +1836,19 @@ hipError_t launch_fft4k(const BatchHdr* hdr, int64_t blocks, const BankDev& b,
   return hipGetLastError();
 }
 
+// Output levels of k_fft4k_search: level r holds block positions 1024 r .. 1024 r + 1023.
+hipError_t launch_fft4k_search(const BatchHdr* hdr, int64_t blocks, const BankDev& b,
+                               const SearchDev& p, hipStream_t s) {
+  const int need = (2 * 4096 - b.L + 1 + 1023) / 1024;
+  if (need <= 5)
+    hipLaunchKernelGGL(k_fft4k_search<5>, dim3((unsigned)blocks), dim3(512), 0, s, hdr, b, p);
+  else if (need <= 7)
+    hipLaunchKernelGGL(k_fft4k_search<7>, dim3((unsigned)blocks), dim3(512), 0, s, hdr, b, p);
+  else
+    hipLaunchKernelGGL(k_fft4k_search<8>, dim3((unsigned)blocks), dim3(512), 0, s, hdr, b, p);
+  return hipGetLastError();
+}
+
 // Register target of the search kernel: BF_FFT_OCC=4 selects the 4-waves-per-SIMD build
 // (a tuning knob; results do not depend on it), else 2.
 int fft_occupancy() {
@@ -1596,7 +1875,7 @@ hipError_t launch_fft_search_t(const BatchHdr* hdr, int64_t blocks, const BankDe
   if (e != hipSuccess) return e;
   if (M == 4096 && fft4k_enabled()) {
     if (p.mode == MODE_ONEPASS) return launch_fft4k<MODE_ONEPASS>(hdr, blocks, b, p, s);
-    return launch_fft4k<MODE_SEARCH>(hdr, blocks, b, p, s);
+    return launch_fft4k_search(hdr, blocks, b, p, s);
   }
   if (p.mode != MODE_SEARCH) return hipErrorInvalidValue;
   if (fft_occupancy() == 4)
@@ -1662,7 +1941,7 @@ hipError_t launch_fft_pass(const BatchHdr* hdr, int64_t blocks, const BankDev& b
 
 int contraction_wgs_per_cu(const BankDev& b) {
   if (b.precision != P_FFT) return 1;
-  if (b.fft_m == 4096 && fft4k_enabled()) return 2;        // k_fft4k: 2 x 4 waves
+  if (b.fft_m == 4096 && fft4k_enabled()) return 2;        // k_fft4k_search: 2 x 8 waves
   const int waves = 4 * fft_occupancy();                    // k_fft_main: waves per CU
   const int wg_waves = std::max(1, b.fft_m / 512);          // M / 8 threads per work-group
   return std::max(1, waves / std::max(1, wg_waves));
