@@ -394,7 +394,8 @@ bf_status run_batch(const bf_bank* bank, const bf_segment* segs, int32_t n_segs,
   if (onepass) {
     // BF_TAILS_MARGIN overrides the predicted-threshold margin (a knob; above 1 it makes the
     // check fail, which exercises the fallback)
-    const float margin = (float)env_double("BF_TAILS_MARGIN", TAILS_MARGIN);
+    const float margin = (float)env_double(
+        "BF_TAILS_MARGIN", b.precision == P_FFT ? TAILS_MARGIN_FFT : TAILS_MARGIN);
     return enqueue_onepass_tail_kernels(bank, sp, sp_t, tab_dev, n_segs, xb, ti.n_items,
                                         margin, stream, te);
   }
@@ -757,13 +758,13 @@ bf_status enqueue_onepass_tail_kernels(const bf_bank* bank, const SearchDev& sp_
   if (b.precision == P_FFT)
     HIP_TRY(launch_fft_pair_list(table_dev, seg_slots, b, stream), "k_fft_pair_list launch");
   HIP_TRY(launch_tails_check(table_dev, seg_slots, b, stream), "k_tails_check launch");
-  // the tails of the series whose check passed: from the kept correlations (direct forms) or
-  // by transforming the listed (block, template) pairs again (FFT form)
+  // the tails from the kept correlations (direct forms) or by transforming the listed (block,
+  // template) pairs again (FFT form)
   if (b.precision == P_FFT)
     HIP_TRY(launch_fft_pairs(table_dev, seg_slots, b, stream), "k_fft4k_pairs launch");
   else
     HIP_TRY(launch_tails_keep(table_dev, seg_slots, b, stream), "k_tails_keep launch");
-  // the tails pass: every work item of a series whose check passed returns at once
+  // the tails pass over what the check flagged; every other work item returns at once
   if (b.precision == P_FFT)
     HIP_TRY(launch_fft_pass(table_dev, main_blocks, b, sp_tails, stream), "k_fft tails launch");
   else

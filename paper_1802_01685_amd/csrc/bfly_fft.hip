@@ -345,15 +345,20 @@ __global__ __launch_bounds__(Plan<M>::T) void k_fft_bank(GridDev g, BankDev b,
 }
 
 // ---- single-pass tail search: predicted lower thresholds ---------------------------------
-// thr_lo[k] = kappa * margin * sqrt(P_k / (n_ok N)), P_k = sum over f in [0, N) of
+// thr_lo[k] = kappa * margin * sqrt(P_k / (n_ok N) * W / n), P_k = sum over f in [0, N) of
 // |H_k(f)|^2 Q(f) (Q from k_qspec, real and even: the bins 1 .. N/2 - 1 count twice), or +inf
-// past the bank's templates and for a series without a non-degenerate offset.
+// past the bank's templates and for a series without a non-degenerate offset.  P_k also holds
+// the partial overlaps at the series' ends: all n + L - 1 of them carry n / W of the energy of
+// the W full windows, which W / n takes out (the median of exact / predicted is 1.000 with it;
+// it was 0.968 without it on a series of 16 template lengths).
 
 __device__ __forceinline__ void pred_store(const SegDesc& sg, int64_t k, const BankDev& b,
                                            double P, int N, float kappa, float margin) {
   const double nok = sg.acf[b.L];
   float v = __builtin_inff();
-  if (k < b.K && nok > 0.0) v = (float)((double)kappa * (double)margin * sqrt(P / (nok * (double)N)));
+  if (k < b.K && nok > 0.0)
+    v = (float)((double)kappa * (double)margin *
+                sqrt(P / (nok * (double)N) * ((double)sg.W / (double)sg.n)));
   sg.thr_lo[k] = v;
 }
 
@@ -988,7 +993,7 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
       if (segs[mid].tile0 <= tt) lo = mid; else hi = mid - 1;
     }
     const SegDesc& sg = segs[lo];
-    // after a single-pass search the tails pass runs only for series whose prediction failed
+    // after a single-pass search the tails pass runs only for flagged series
     if (MODE == MODE_TAILS && sg.redo && sg.redo[0] == 0u) continue;
     const int64_t blk = tt - sg.tile0;
     const int tau_base = (int)(blk * valid);     // series are shorter than 2^31 samples
@@ -1551,7 +1556,7 @@ __global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restr
 }
 
 // The tails of the (block, template) pairs the single pass of k_fft4k listed, for every
-// series whose check passed (redo = 0; a flagged series gets the full tails pass instead).
+// series not flagged (redo = 0; a flagged series gets the full tails pass instead).
 // Per pair the transform of k_fft4k with the same operations in the same order, so rho is
 // the same bit for bit, then the compare against kappa sigma_k.  Work unit = (series, shard
 // of the pair list); a work-group takes a shard's pairs one after another.  Two work-groups
@@ -1746,7 +1751,8 @@ bool fft_onepass_available(const BankDev& b) {
 namespace {
 
 // The single pass's list of (block, template) pairs holding a correlation above the kept
-// bound: the pairs with the flag bit in any of their four wave sums.  Shard s takes the
+// bound: the pairs with the flag bit in any of their four wave sums, and every block of a
+// template whose exact threshold lies below that bound.  Shard s takes the
 // 64-template groups g with g mod 256 = s, block by block, so a shard's pairs come in runs
 // of one block (k_fft4k_pairs reloads a block's spectrum only when the block changes), the
 // shards share the flagged templates evenly wherever they cluster, and the list is the same
@@ -1773,7 +1779,7 @@ __global__ __launch_bounds__(256) void k_fft_pair_list(const BatchHdr* __restric
       // words are whatever the workspace held
       if (g < n_groups && k < b.K)
         fl = ((rows[k] | rows[b.K_pad + k] | rows[2 * b.K_pad + k] | rows[3 * b.K_pad + k]) &
-              SIG_FLAG) != 0ull;
+              SIG_FLAG) != 0ull || !(sg.thr[k] >= sg.thr_lo[k]);
       const unsigned long long bal = __ballot(fl);
       if (lane == 0) cnt[w] = (unsigned int)__popcll(bal);
       __syncthreads();

@@ -114,7 +114,7 @@ struct SegDesc {
   float* c_rho;                  // [cand_cap] candidate rho (signed; unused by the FFT form)
   unsigned long long* n_cand;    // [CAND_SHARDS] candidates found per shard
   int64_t cand_cap;              // CAND_SHARDS shards of cand_cap / CAND_SHARDS entries
-  uint32_t* redo;                // [1] 1: the prediction did not hold, run the tails pass
+  uint32_t* redo;                // [1] what the tails pass still has to do: REDO_ALL, REDO_TILES
   float* zloc;                   // [n] the locally normalised series
   double* acf_part;              // [ACF_CHUNKS][L] lag sums over chunks of the series
   double* acf;                   // [L + 1] lag sums, then the non-degenerate offset count
@@ -125,6 +125,9 @@ constexpr int ACF_CHUNKS = 16;
 // counter: appends to one global counter from every work-group contend (device-scope atomics
 // on one address serialise across the XCDs).
 constexpr int CAND_SHARDS = 256;
+// Tails pass after a single-pass search: the whole series (its candidates did not fit), or the
+// template tiles whose prediction did not hold.
+constexpr uint32_t REDO_ALL = 1u, REDO_TILES = 2u;
 
 // The level subtracted from every staged sample: the mean of the series over its finite
 // samples, from its prefix sums, rounded to a multiple of q = 2^floor(log2 sigma), sigma the
@@ -207,10 +210,12 @@ enum MainMode { MODE_SEARCH = 0, MODE_SIGMA = 1, MODE_TAILS = 2, MODE_ONEPASS = 
 
 // Single-pass tail search: the fraction of the predicted sigma below which candidates are
 // kept (the prediction is checked against the exact sigma after the pass).  Only the time
-// depends on it: the exact sigma stayed within 0.989-1.08 of the prediction on the
-// light-curve, strain and batch workloads, and a lower margin keeps (and, in the FFT form,
-// transforms again) more: 3.1% of the (block, template) pairs at 0.9, 0.95% at 0.95.
+// depends on it.  exact / predicted over the templates has its 0.1% quantile at 0.986 on 16 s
+// of white strain (65,536 x 4096) and 0.986-0.990 on a 64 s light curve and its control, its
+// 1% quantile at 0.975-0.987 on series of 6 to 14 templates' length; a template below the
+// margin costs the FFT form its blocks once more and the direct forms its tile of 64.
 constexpr float TAILS_MARGIN = 0.95f;
+constexpr float TAILS_MARGIN_FFT = 0.97f;
 
 // Bytes of the quantised templates, of the per-template side tables, and of the whole bank
 // allocation (templates, side tables, then a 256-byte status word).
@@ -261,16 +266,16 @@ hipError_t launch_fft_search(const BatchHdr* hdr, int64_t blocks, const BankDev&
 // (k_qspec), and per template kappa * margin * sqrt(sum_f |H_k(f)|^2 Q(f) / (n_ok pred_n))
 // from the bank's spectra (FFT form) or from spectra made on the fly (direct forms).  After
 // the pass that sums rho^2 and keeps candidates above those thresholds: k_tails_check flags
-// a series whose exact thresholds fall below the predicted ones (or whose candidates
-// overflowed), and k_tails_keep (direct forms) moves the candidates above the exact
-// thresholds into the tail lists of every series not flagged, or launch_fft_pairs (FFT form)
-// transforms its listed pairs again; the tails pass then runs only for flagged series.
+// a series whose candidates overflowed (direct forms: and the template tiles whose exact
+// thresholds fall below the predicted ones), and k_tails_keep (direct forms) moves the other
+// candidates above the exact thresholds into the tail lists, or launch_fft_pairs (FFT form)
+// transforms the listed pairs again; the tails pass then runs only for what is flagged.
 int pred_points(const BankDev& b);
 // The FFT form's search kernel has the single-pass mode (N = 8192, fewer than 2^16
 // templates per f0 bin).  Its candidates are (block, template) pairs, not correlations: the
 // pass flags them in its per-wave rho^2 sums, launch_fft_pair_list lists them per shard (c_tau
 // holds the block and c_k the template, n_cand the count), and launch_fft_pairs extracts the
-// tails of the listed pairs of every series whose check passed.
+// tails of the listed pairs of every series not flagged.
 bool fft_onepass_available(const BankDev& b);
 // Work-groups of the bank's contraction kernel that are resident on one CU (the grid of a
 // persistent launch is the CU count times this).

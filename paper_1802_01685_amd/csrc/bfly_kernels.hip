@@ -922,8 +922,9 @@ __device__ __forceinline__ void main_item(const BatchHdr* __restrict__ hdr, int6
     if (segs[mid].tile0 <= tt) lo = mid; else hi = mid - 1;
   }
   const SegDesc& sg = segs[lo];
-  // after a single-pass search the tails pass runs only for series whose prediction failed
-  if (MODE == MODE_TAILS && sg.redo && sg.redo[0] == 0u) return;
+  // after a single-pass search the tails pass runs only for what k_tails_check flagged
+  const uint32_t redo = MODE == MODE_TAILS && sg.redo ? sg.redo[0] : REDO_ALL;
+  if (MODE == MODE_TAILS && redo == 0u) return;
   const int64_t tau0 = (tt - sg.tile0) * (32 * NB * WG_WAVES);
   const int b_lo = (int)((int64_t)r * b.n_bins / n_ranges);
   const int b_hi = (int)((int64_t)(r + 1) * b.n_bins / n_ranges);
@@ -1161,6 +1162,10 @@ __device__ __forceinline__ void main_item(const BatchHdr* __restrict__ hdr, int6
   const int nfd = b.n_fdot;
 
   for (int64_t kt = tile_lo; kt < tile_hi; ++kt) {
+    if constexpr (MODE == MODE_TAILS) {
+      static_assert(32 * MB == TILE_K, "the flagged tiles are this pass's tiles");
+      if (!(redo & REDO_ALL) && !(sg.thr_lo[kt * TILE_K] < 0.0f)) continue;
+    }
     f32x16 acc[MB][NB];
 #pragma unroll
     for (int t = 0; t < MB; ++t)

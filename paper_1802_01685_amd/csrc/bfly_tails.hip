@@ -11,9 +11,11 @@
 // every (block, k) pair holding one) while it sums the exact rho^2; afterwards the exact
 // thresholds kappa * sigma_k select the tails among the candidates (the FFT form transforms
 // the listed pairs again).  That is exact whenever no exact threshold lies below its
-// predicted one and the candidates fit: k_tails_check verifies both per series and flags a
-// series for which either fails, and the ordinary tails pass then runs for it.  Either way
-// the tails, sigma and counts are those of the two-pass search, bit for bit.
+// predicted one and the candidates fit.  Templates for which the first fails are handled by
+// themselves: the FFT form lists all their blocks for the second transform, the direct forms
+// run the ordinary tails pass over the template tiles that hold one; a series whose candidates
+// did not fit gets the whole pass.  Either way the tails, sigma and counts are those of the
+// two-pass search, bit for bit.
 #include "bfly_internal.h"
 
 #include <hip/hip_runtime.h>
@@ -134,27 +136,38 @@ __global__ __launch_bounds__(256) void k_qspec(const BatchHdr* __restrict__ hdr,
   sg.qspec[f] = (float)q;
 }
 
-// Per series: redo = 1 if any exact threshold lies below its predicted lower threshold, or
-// the candidates of a shard did not fit.
+// Per series: REDO_ALL if the candidates of a shard did not fit; direct forms: REDO_TILES if an
+// exact threshold lies below its predicted lower one, with the first bound of each such tile
+// of TILE_K templates overwritten by -1 (bounds are not negative).  One wave per tile.
 __global__ __launch_bounds__(256) void k_tails_check(const BatchHdr* __restrict__ hdr, BankDev b) {
   if ((int)blockIdx.y >= hdr->n_segs) return;
   const SegDesc& sg = hdr_segs(hdr)[blockIdx.y];
   if (!sg.redo) return;
-  bool bad = false;
   const int64_t per = sg.cand_cap / CAND_SHARDS;
   if (blockIdx.x == 0 && threadIdx.x < CAND_SHARDS && (int64_t)sg.n_cand[threadIdx.x] > per)
-    bad = true;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < b.K; k += stride)
-    if (!(sg.thr[k] >= sg.thr_lo[k])) bad = true;
-  if (bad) atomicOr(sg.redo, 1u);
+    atomicOr(sg.redo, REDO_ALL);
+  if (b.precision == P_FFT) return;   // k_fft_pair_list lists those templates' blocks
+  static_assert(TILE_K == WAVE, "one lane per template of a tile");
+  const int lane = threadIdx.x & 63;
+  const int64_t n_tiles = b.K_pad / TILE_K;
+  for (int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < n_tiles;
+       t += (int64_t)gridDim.x * 4) {
+    const int64_t k = t * TILE_K + lane;
+    const bool bad = k < b.K && !(sg.thr[k] >= sg.thr_lo[k]);
+    if (__any(bad) && lane == 0) {
+      sg.thr_lo[t * TILE_K] = -1.0f;
+      atomicOr(sg.redo, REDO_TILES);
+    }
+  }
 }
 
-// Per series not flagged: every candidate above its exact threshold is a tail.
+// Every candidate above its exact threshold is a tail, unless the tails pass takes the series
+// or the candidate's tile.
 __global__ __launch_bounds__(256) void k_tails_keep(const BatchHdr* __restrict__ hdr, BankDev b) {
   if ((int)blockIdx.y >= hdr->n_segs) return;
   const SegDesc& sg = hdr_segs(hdr)[blockIdx.y];
-  if (!sg.redo || sg.redo[0] != 0u) return;
+  if (!sg.redo || (sg.redo[0] & REDO_ALL)) return;
+  const bool tiles = sg.redo[0] != 0u;
   const int64_t per = sg.cand_cap / CAND_SHARDS;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < per * CAND_SHARDS;
@@ -162,7 +175,7 @@ __global__ __launch_bounds__(256) void k_tails_keep(const BatchHdr* __restrict__
     if ((unsigned long long)(i % per) >= sg.n_cand[i / per]) continue;
     const int32_t kl = sg.c_k[i];
     const float rf = sg.c_rho[i];
-    if (fabsf(rf) > sg.thr[kl]) {
+    if (fabsf(rf) > sg.thr[kl] && !(tiles && sg.thr_lo[kl & ~(TILE_K - 1)] < 0.0f)) {
       const unsigned long long slot = atomicAdd(sg.n_tails, 1ull);
       if ((int64_t)slot < sg.tail_cap) {
         sg.t_tau[slot] = sg.c_tau[i];
@@ -205,7 +218,7 @@ hipError_t launch_qspec(const BatchHdr* hdr, int32_t seg_slots, int L, int pred_
 
 hipError_t launch_tails_check(const BatchHdr* hdr, int32_t seg_slots, const BankDev& b,
                               hipStream_t s) {
-  const int64_t xb = (b.K + 255) / 256;
+  const int64_t xb = (b.K_pad + 255) / 256;
   hipLaunchKernelGGL(k_tails_check, dim3((unsigned)(xb < 1024 ? (xb > 0 ? xb : 1) : 1024), (unsigned)seg_slots),
                      dim3(256), 0, s, hdr, b);
   return hipGetLastError();
