@@ -387,7 +387,7 @@ bf_status run_batch(const bf_bank* bank, const bf_segment* segs, int32_t n_segs,
     return st;
   const int32_t xb =
       (int32_t)std::min<int64_t>(std::max<int64_t>((ti.max_words + 255) / 256, 1), 2048);
-  if (!with_tails) return enqueue_kernels(b, sp, tab_dev, n_segs, xb, ti.n_items, stream, te);
+  if (!with_tails) return enqueue_kernels(b, sp, tab_dev, n_segs, xb, ti.max_n, ti.n_items, stream, te);
   SearchDev sp_t = sp;
   sp_t.mode = MODE_TAILS;
   if (b.precision != P_FFT) HIP_TRY(prepare_main(b, sp_t), "hipFuncSetAttribute(k_main)");
@@ -396,10 +396,10 @@ bf_status run_batch(const bf_bank* bank, const bf_segment* segs, int32_t n_segs,
     // check fail, which exercises the fallback)
     const float margin = (float)env_double(
         "BF_TAILS_MARGIN", b.precision == P_FFT ? TAILS_MARGIN_FFT : TAILS_MARGIN);
-    return enqueue_onepass_tail_kernels(bank, sp, sp_t, tab_dev, n_segs, xb, ti.n_items,
-                                        margin, stream, te);
+    return enqueue_onepass_tail_kernels(bank, sp, sp_t, tab_dev, n_segs, xb, ti.max_n,
+                                        ti.n_items, margin, stream, te);
   }
-  return enqueue_tail_kernels(b, sp, sp_t, tab_dev, n_segs, xb, ti.n_items, stream, te);
+  return enqueue_tail_kernels(b, sp, sp_t, tab_dev, n_segs, xb, ti.max_n, ti.n_items, stream, te);
 }
 
 size_t series_ws_bytes(const BankDev& b, int64_t n, bool tails) {
@@ -650,6 +650,7 @@ TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s,
     d.acf = one ? s[i].acf : nullptr;
     d.qspec = one ? s[i].qspec : nullptr;
     ti.max_W = std::max(ti.max_W, d.W);
+    ti.max_n = std::max(ti.max_n, d.n);
     ti.max_words = std::max(ti.max_words, std::max(d.W, d.spec ? d.spec_rows * b.n_bins : 0));
   }
   std::memset(hdr, 0, sizeof(BatchHdr));
@@ -686,16 +687,17 @@ TimingSet* timing_slot(int dev, bf_status* st) {
   return te;
 }
 
-// x_blocks: blocks per series of the grid-stride kernels (any value >= 1 is correct);
+// x_blocks: blocks per series of the grid-stride kernels (any value >= 1 is correct); max_n:
+// samples of the longest series, sizes the prefix sums' grid (likewise);
 // main_blocks: work-groups of the contraction kernel (n_items for one item each).
 bf_status enqueue_kernels(const BankDev& b, const SearchDev& sp, const BatchHdr* table_dev,
-                          int32_t seg_slots, int32_t x_blocks, int64_t main_blocks,
-                          hipStream_t stream, TimingSet* te) {
+                          int32_t seg_slots, int32_t x_blocks, int64_t max_n,
+                          int64_t main_blocks, hipStream_t stream, TimingSet* te) {
   const int32_t xb = x_blocks > 0 ? x_blocks : 1;
   if (te) HIP_TRY(hipEventRecord(te->ev[0], stream), "hipEventRecord");
   HIP_TRY(launch_zero(table_dev, seg_slots, xb, b, sp, stream), "k_zero launch");
   if (te) HIP_TRY(hipEventRecord(te->ev[1], stream), "hipEventRecord");
-  HIP_TRY(launch_prefix(table_dev, seg_slots, stream), "k_prefix launch");
+  HIP_TRY(launch_prefix(table_dev, seg_slots, max_n, stream), "k_prefix launch");
   if (te) HIP_TRY(hipEventRecord(te->ev[2], stream), "hipEventRecord");
   HIP_TRY(launch_norms(table_dev, seg_slots, xb, b.L, sp.norm, stream), "k_norms launch");
   if (te) HIP_TRY(hipEventRecord(te->ev[3], stream), "hipEventRecord");
@@ -711,10 +713,10 @@ bf_status enqueue_kernels(const BankDev& b, const SearchDev& sp, const BatchHdr*
 
 bf_status enqueue_tail_kernels(const BankDev& b, const SearchDev& sp_sigma,
                                const SearchDev& sp_tails, const BatchHdr* table_dev,
-                               int32_t seg_slots, int32_t x_blocks, int64_t main_blocks,
+                               int32_t seg_slots, int32_t x_blocks, int64_t max_n, int64_t main_blocks,
                                hipStream_t stream, TimingSet* te) {
-  bf_status st = enqueue_kernels(b, sp_sigma, table_dev, seg_slots, x_blocks, main_blocks,
-                                 stream, te);
+  bf_status st = enqueue_kernels(b, sp_sigma, table_dev, seg_slots, x_blocks, max_n,
+                                 main_blocks, stream, te);
   if (st != BF_OK) return st;
   if (b.precision == P_FFT) {
     // the FFT form: a sigma pass and a tails pass over the search's data spectra
@@ -732,14 +734,14 @@ bf_status enqueue_tail_kernels(const BankDev& b, const SearchDev& sp_sigma,
 
 bf_status enqueue_onepass_tail_kernels(const bf_bank* bank, const SearchDev& sp_pass,
                                        const SearchDev& sp_tails, const BatchHdr* table_dev,
-                                       int32_t seg_slots, int32_t x_blocks, int64_t main_blocks,
+                                       int32_t seg_slots, int32_t x_blocks, int64_t max_n, int64_t main_blocks,
                                        float margin, hipStream_t stream, TimingSet* te) {
   const BankDev& b = bank->dev;
   const int32_t xb = x_blocks > 0 ? x_blocks : 1;
   if (te) HIP_TRY(hipEventRecord(te->ev[0], stream), "hipEventRecord");
   HIP_TRY(launch_zero(table_dev, seg_slots, xb, b, sp_pass, stream), "k_zero launch");
   if (te) HIP_TRY(hipEventRecord(te->ev[1], stream), "hipEventRecord");
-  HIP_TRY(launch_prefix(table_dev, seg_slots, stream), "k_prefix launch");
+  HIP_TRY(launch_prefix(table_dev, seg_slots, max_n, stream), "k_prefix launch");
   if (te) HIP_TRY(hipEventRecord(te->ev[2], stream), "hipEventRecord");
   HIP_TRY(launch_norms(table_dev, seg_slots, xb, b.L, sp_pass.norm, stream), "k_norms launch");
   // the predictor

@@ -240,7 +240,8 @@ inline size_t bank_total_bytes(const BankDev& b) {
 hipError_t launch_bank_gen(const GridDev& g, const BankDev& b, void* dst, hipStream_t s);
 hipError_t launch_zero(const BatchHdr* hdr, int32_t seg_slots, int32_t x_blocks,
                        const BankDev& b, const SearchDev& p, hipStream_t s);
-hipError_t launch_prefix(const BatchHdr* hdr, int32_t seg_slots, hipStream_t s);
+// max_n: samples of the longest series (any value >= 1 is correct; it sizes the grid).
+hipError_t launch_prefix(const BatchHdr* hdr, int32_t seg_slots, int64_t max_n, hipStream_t s);
 hipError_t launch_norms(const BatchHdr* hdr, int32_t seg_slots, int32_t x_blocks, int L,
                         int norm, hipStream_t s);
 hipError_t prepare_main(const BankDev& b, const SearchDev& p);

@@ -1,9 +1,10 @@
 // HIP kernels of the butterfly-filtering search, written for gfx950 (MI355X).
 //
 //   k_bank_gen   float64 chirp templates -> quantised bank in the MFMA operand layout
-//   k_zero       clears the running maxima, spectrogram, spectrum sums and histograms
+//   k_zero       clears the spectrogram, spectrum sums and histograms; sums of sample chunks
 //   k_prefix     float64 (double-double) prefix sums of x and x^2, non-finite counts
-//   k_norms      per-window energies from the prefix sums -> 1/sqrt(E), degenerate flags
+//   k_norms      per-window energies from the prefix sums -> 1/sqrt(E), degenerate flags;
+//                clears the running maxima
 //   k_main       the template x window contraction on MFMA with the reductions fused in
 //   k_finalize   butterfly output, histogram of maxima, spectrum
 //
@@ -278,7 +279,51 @@ hipError_t launch_bank_gen(const GridDev& g, const BankDev& b, void* dst, hipStr
 }
 
 // ---------------------------------------------------------------------------------------
-// Clearing: running maxima, spectrogram, spectrum sums, histogram, degenerate count.
+// Prefix sums of x and x^2 in double-double (non-finite samples count as 0 and are counted
+// separately), in two launches: k_zero also sums every chunk of PRE_CHUNK samples, and k_prefix
+// adds the chunks before its own and scans within it, so every CU takes part (one work-group
+// per series scanning chunk after chunk took 15 us for 2,048 samples, 186 us for 65,536 and
+// 1.1 ms for 397,311).  The sums of float samples and of their squares are exact in
+// double-double unless the samples span more than about 2^20 in magnitude, so the order of
+// the additions does not show.  The chunk sums live in the running-maxima buffer until
+// k_norms clears it: 40 bytes per 2,048 samples of a series of W + L - 1 fit its
+// round_up(8 W, 256) bytes for every L <= 8192.
+// ---------------------------------------------------------------------------------------
+constexpr int PRE_E = 8;                   // consecutive samples per thread
+constexpr int PRE_CHUNK = 256 * PRE_E;
+static_assert(40 * ((32 + MAX_L - 1 + PRE_CHUNK - 1) / PRE_CHUNK) <= 256, "chunk sums fit");
+
+struct Sums {
+  dd s1, s2;
+  int c;
+};
+__device__ __forceinline__ Sums sums_add(const Sums& a, const Sums& b) {
+  return {dd_add(a.s1, b.s1), dd_add(a.s2, b.s2), a.c + b.c};
+}
+__device__ __forceinline__ void sums_take(Sums& a, float v) {
+  const bool fin = isfinite(v);
+  const double d = fin ? (double)v : 0.0;
+  a.s1 = dd_add(a.s1, {d, 0.0});
+  a.s2 = dd_add(a.s2, {d * d, 0.0});  // exact for a float
+  a.c += fin ? 0 : 1;
+}
+// Total over the 256 threads, in every thread; part is overwritten.
+__device__ __forceinline__ Sums block_sums(Sums v, Sums (&part)[4]) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const Sums u = {{__shfl_xor(v.s1.hi, o, 64), __shfl_xor(v.s1.lo, o, 64)},
+                    {__shfl_xor(v.s2.hi, o, 64), __shfl_xor(v.s2.lo, o, 64)},
+                    __shfl_xor(v.c, o, 64)};
+    v = sums_add(v, u);
+  }
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return sums_add(sums_add(part[0], part[1]), sums_add(part[2], part[3]));
+}
+
+// ---------------------------------------------------------------------------------------
+// Clearing: spectrogram, spectrum sums, histogram, degenerate count; and the chunk sums.
 // grid = (X, n_segs); each series clears its own buffers with a grid-stride loop.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_zero(const BatchHdr* __restrict__ hdr, BankDev b,
@@ -287,7 +332,26 @@ __global__ __launch_bounds__(256) void k_zero(const BatchHdr* __restrict__ hdr, 
   const SegDesc& sg = hdr_segs(hdr)[blockIdx.y];
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int64_t i = t0; i < sg.W; i += stride) sg.mkey[i] = 0ull;
+  __shared__ Sums part[4];
+  double* tot = (double*)sg.mkey;
+  for (int64_t c0 = (int64_t)blockIdx.x * PRE_CHUNK; c0 < sg.n;
+       c0 += (int64_t)gridDim.x * PRE_CHUNK) {
+    Sums v = {{0.0, 0.0}, {0.0, 0.0}, 0};
+#pragma unroll
+    for (int e = 0; e < PRE_E; ++e) {
+      const int64_t i = c0 + e * 256 + threadIdx.x;
+      sums_take(v, i < sg.n ? sg.x[i] : 0.0f);
+    }
+    v = block_sums(v, part);
+    if (threadIdx.x == 0) {
+      double* o = tot + 5 * (c0 / PRE_CHUNK);
+      o[0] = v.s1.hi;
+      o[1] = v.s1.lo;
+      o[2] = v.s2.hi;
+      o[3] = v.s2.lo;
+      o[4] = (double)v.c;
+    }
+  }
   if (sg.spec) {
     const int64_t ns = sg.spec_rows * b.n_bins;
     for (int64_t i = t0; i < ns; i += stride) sg.spec[i] = 0.0f;
@@ -317,125 +381,88 @@ hipError_t launch_zero(const BatchHdr* hdr, int32_t seg_slots, int32_t x_blocks,
 }
 
 // ---------------------------------------------------------------------------------------
-// Prefix sums: one 1024-thread work-group per series scans x in tiles of 1024 x PRE_E
-// samples, carrying double-double sums of x and x^2 (non-finite samples count as 0 and are
-// counted separately).  pre[i] holds the sums over x[0..i).  Each thread sums its PRE_E
-// consecutive samples, the threads' totals are scanned across the wave by shuffles and
-// across the 16 waves by thread 0, and each thread then runs through its samples again
-// (from cache) from the sum of everything before them, writing each prefix.
+// pre[i], cnt[i]: the sums over x[0..i).  grid = (X, n_segs); a work-group takes runs of
+// chunks (one chunk each below 2048 chunks; the order of the additions depends on the series
+// alone, not on the grid): the chunk sums before the run, then chunk after chunk each thread's
+// PRE_E samples, the threads' totals scanned across the wave by shuffles and the waves' totals
+// through LDS.
 // ---------------------------------------------------------------------------------------
-constexpr int PRE_E = 16;
-
-__global__ __launch_bounds__(1024) void k_prefix(const BatchHdr* __restrict__ hdr) {
-  if ((int)blockIdx.x >= hdr->n_segs) return;
-  const SegDesc& sg = hdr_segs(hdr)[blockIdx.x];
-  __shared__ dd w1[16], w2[16];
-  __shared__ int wc[16];
-  __shared__ dd c1s, c2s;
-  __shared__ int ccs;
+__global__ __launch_bounds__(256) void k_prefix(const BatchHdr* __restrict__ hdr) {
+  if ((int)blockIdx.y >= hdr->n_segs) return;
+  const SegDesc& sg = hdr_segs(hdr)[blockIdx.y];
+  __shared__ Sums part[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) {
-    c1s = {0.0, 0.0};
-    c2s = {0.0, 0.0};
-    ccs = 0;
+  const int64_t n_chunks = (sg.n + PRE_CHUNK - 1) / PRE_CHUNK;
+  const int64_t run = (n_chunks + 2047) / 2048;
+  const double* tot = (const double*)sg.mkey;
+  if (blockIdx.x == 0 && tid == 0) {
     sg.pre[0] = 0.0;
     sg.pre[1] = 0.0;
     sg.pre[2] = 0.0;
     sg.pre[3] = 0.0;
     sg.cnt[0] = 0;
   }
-  __syncthreads();
-  for (int64_t base = 0; base < sg.n; base += 1024 * PRE_E) {
-    const int64_t i0 = base + (int64_t)tid * PRE_E;
-    // this thread's totals over its PRE_E samples
-    dd s1 = {0.0, 0.0}, s2 = {0.0, 0.0};
-    int c = 0;
-#pragma unroll
-    for (int e = 0; e < PRE_E; ++e) {
-      const int64_t i = i0 + e;
-      const float v = i < sg.n ? sg.x[i] : 0.0f;
-      const bool fin = isfinite(v);
-      const double a = fin ? (double)v : 0.0;
-      s1 = dd_add(s1, {a, 0.0});
-      s2 = dd_add(s2, {a * a, 0.0});  // a*a is exact for a float a
-      c += (i < sg.n && !fin) ? 1 : 0;
+  for (int64_t c_lo = blockIdx.x * run; c_lo < n_chunks; c_lo += gridDim.x * run) {
+    const int64_t c_hi = c_lo + run < n_chunks ? c_lo + run : n_chunks;
+    Sums base = {{0.0, 0.0}, {0.0, 0.0}, 0};
+    for (int64_t c = tid; c < c_lo; c += 256) {
+      const double* o = tot + 5 * c;
+      base = sums_add(base, {{o[0], o[1]}, {o[2], o[3]}, (int)o[4]});
     }
-    // inclusive scan of the thread totals across the wave
-    dd t1 = s1, t2 = s2;
-    int tc = c;
+    base = block_sums(base, part);
+    for (int64_t c = c_lo; c < c_hi; ++c) {
+      const int64_t i0 = c * PRE_CHUNK + (int64_t)tid * PRE_E;
+      float v[PRE_E];
+      Sums t = {{0.0, 0.0}, {0.0, 0.0}, 0};   // this thread's samples
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const dd u1 = {__shfl_up(t1.hi, off, 64), __shfl_up(t1.lo, off, 64)};
-      const dd u2 = {__shfl_up(t2.hi, off, 64), __shfl_up(t2.lo, off, 64)};
-      const int uc = __shfl_up(tc, off, 64);
-      if (lane >= off) {
-        t1 = dd_add(u1, t1);
-        t2 = dd_add(u2, t2);
-        tc += uc;
+      for (int e = 0; e < PRE_E; ++e) {
+        v[e] = i0 + e < sg.n ? sg.x[i0 + e] : 0.0f;
+        sums_take(t, v[e]);
+      }
+      // inclusive scan across the wave
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const Sums u = {{__shfl_up(t.s1.hi, off, 64), __shfl_up(t.s1.lo, off, 64)},
+                        {__shfl_up(t.s2.hi, off, 64), __shfl_up(t.s2.lo, off, 64)},
+                        __shfl_up(t.c, off, 64)};
+        if (lane >= off) t = sums_add(u, t);
+      }
+      // exclusive: the inclusive scan of the previous lane (0 on lane 0)
+      Sums q = {{__shfl_up(t.s1.hi, 1, 64), __shfl_up(t.s1.lo, 1, 64)},
+                {__shfl_up(t.s2.hi, 1, 64), __shfl_up(t.s2.lo, 1, 64)},
+                __shfl_up(t.c, 1, 64)};
+      if (lane == 0) q = {{0.0, 0.0}, {0.0, 0.0}, 0};
+      __syncthreads();   // the previous chunk's (and the base's) totals have been read
+      if (lane == 63) part[wave] = t;
+      __syncthreads();
+      Sums before = base;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (w == wave) before = base;
+        base = sums_add(base, part[w]);
+      }
+      q = sums_add(before, q);
+#pragma unroll
+      for (int e = 0; e < PRE_E; ++e) {
+        const int64_t i = i0 + e;
+        if (i < sg.n) {
+          sums_take(q, v[e]);
+          double* o = sg.pre + (i + 1) * 4;
+          o[0] = q.s1.hi;
+          o[1] = q.s1.lo;
+          o[2] = q.s2.hi;
+          o[3] = q.s2.lo;
+          sg.cnt[i + 1] = q.c;
+        }
       }
     }
-    // exclusive: the inclusive scan of the previous lane (0 on lane 0)
-    dd x1 = {__shfl_up(t1.hi, 1, 64), __shfl_up(t1.lo, 1, 64)};
-    dd x2 = {__shfl_up(t2.hi, 1, 64), __shfl_up(t2.lo, 1, 64)};
-    int xc = __shfl_up(tc, 1, 64);
-    if (lane == 0) {
-      x1 = {0.0, 0.0};
-      x2 = {0.0, 0.0};
-      xc = 0;
-    }
-    if (lane == 63) {
-      w1[wave] = t1;
-      w2[wave] = t2;
-      wc[wave] = tc;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      dd r1 = c1s, r2 = c2s;
-      int rc = ccs;
-      for (int w = 0; w < 16; ++w) {
-        const dd a1 = w1[w], a2 = w2[w];
-        const int ac = wc[w];
-        w1[w] = r1;
-        w2[w] = r2;
-        wc[w] = rc;
-        r1 = dd_add(r1, a1);
-        r2 = dd_add(r2, a2);
-        rc += ac;
-      }
-      c1s = r1;
-      c2s = r2;
-      ccs = rc;
-    }
-    __syncthreads();
-    // everything before this thread's first sample: the carry and earlier waves (from
-    // LDS), then the earlier threads of this wave
-    dd q1 = dd_add(w1[wave], x1);
-    dd q2 = dd_add(w2[wave], x2);
-    int qc = wc[wave] + xc;
-#pragma unroll
-    for (int e = 0; e < PRE_E; ++e) {
-      const int64_t i = i0 + e;
-      if (i < sg.n) {
-        const float v = sg.x[i];
-        const bool fin = isfinite(v);
-        const double a = fin ? (double)v : 0.0;
-        q1 = dd_add(q1, {a, 0.0});
-        q2 = dd_add(q2, {a * a, 0.0});
-        qc += fin ? 0 : 1;
-        double* o = sg.pre + (i + 1) * 4;
-        o[0] = q1.hi;
-        o[1] = q1.lo;
-        o[2] = q2.hi;
-        o[3] = q2.lo;
-        sg.cnt[i + 1] = qc;
-      }
-    }
-    __syncthreads();
   }
 }
 
-hipError_t launch_prefix(const BatchHdr* hdr, int32_t seg_slots, hipStream_t s) {
-  hipLaunchKernelGGL(k_prefix, dim3((unsigned)seg_slots), dim3(1024), 0, s, hdr);
+hipError_t launch_prefix(const BatchHdr* hdr, int32_t seg_slots, int64_t max_n, hipStream_t s) {
+  const int64_t xb = (max_n + PRE_CHUNK - 1) / PRE_CHUNK;
+  hipLaunchKernelGGL(k_prefix, dim3((unsigned)(xb < 1 ? 1 : xb < 2048 ? xb : 2048), (unsigned)seg_slots),
+                     dim3(256), 0, s, hdr);
   return hipGetLastError();
 }
 
@@ -472,6 +499,7 @@ __global__ __launch_bounds__(256) void k_norms(const BatchHdr* __restrict__ hdr,
     }
     const bool degenerate = (nc > 0) || !(R > 0.0) || !(E > 1e-12 * R) || !isfinite(E);
     sg.inv_norm[tau] = degenerate ? 0.0 : 1.0 / sqrt(E);
+    sg.mkey[tau] = 0ull;   // running maxima (until here the chunk sums of k_zero)
   }
 }
 

@@ -86,6 +86,7 @@ inline int64_t fft_blocks(const BankDev& b, int64_t W) {
 // Fills a host batch table (hdr followed by the SegDescs) for the series s[0..n-1].
 struct TableInfo {
   int64_t max_W = 0;
+  int64_t max_n = 0;
   int64_t max_words = 0;
   int64_t n_items = 0;
 };
@@ -124,7 +125,8 @@ TimingSet* timing_slot(int device, bf_status* st);
 // Enqueues the five kernels of a search on `stream`, reading the batch table at table_dev.
 // prepare_main(b, sp) must have been called once before (outside any stream capture).
 bf_status enqueue_kernels(const BankDev& b, const SearchDev& sp, const BatchHdr* table_dev,
-                          int32_t seg_slots, int32_t x_blocks, int64_t main_blocks,
+                          int32_t seg_slots, int32_t x_blocks, int64_t max_n,
+                          int64_t main_blocks,
                           hipStream_t stream, TimingSet* te);
 // The tail search: the kernels above with the contraction in MODE_SIGMA, then k_sigma and
 // the MODE_TAILS contraction (sp_sigma and sp_tails differ only in mode).
@@ -134,11 +136,13 @@ bf_status enqueue_kernels(const BankDev& b, const SearchDev& sp, const BatchHdr*
 // whose check failed (its work-groups return at once for the others).
 bf_status enqueue_onepass_tail_kernels(const bf_bank* bank, const SearchDev& sp_pass,
                                        const SearchDev& sp_tails, const BatchHdr* table_dev,
-                                       int32_t seg_slots, int32_t x_blocks, int64_t main_blocks,
+                                       int32_t seg_slots, int32_t x_blocks, int64_t max_n,
+                          int64_t main_blocks,
                                        float margin, hipStream_t stream, TimingSet* te);
 bf_status enqueue_tail_kernels(const BankDev& b, const SearchDev& sp_sigma,
                                const SearchDev& sp_tails, const BatchHdr* table_dev,
-                               int32_t seg_slots, int32_t x_blocks, int64_t main_blocks,
+                               int32_t seg_slots, int32_t x_blocks, int64_t max_n,
+                          int64_t main_blocks,
                                hipStream_t stream, TimingSet* te);
 
 }  // namespace bfly

@@ -405,7 +405,7 @@ bf_status bf_server_create(const bf_bank* bank, const bf_server_desc* desc, bf_s
                                      t.stream);
       bf_status kst = ce == hipSuccess
                           ? enqueue_kernels(bank->dev, s->sp, t.table_dev, desc->max_slots,
-                                            s->x_blocks,
+                                            s->x_blocks, s->x_blocks * (int64_t)2048,
                                             (int64_t)s->slots * contraction_wgs_per_cu(bank->dev),
                                             t.stream, nullptr)
                           : hip_error(ce, "hipMemcpyAsync(capture)");
