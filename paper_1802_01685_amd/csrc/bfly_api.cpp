@@ -575,9 +575,10 @@ int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots) {
 }
 
 constexpr int XCDS = 8;
-int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm) {
+int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, int tn) {
   double best_cost = 1e300;
   int32_t best_r = 1;
+  const int64_t conc = (int64_t)slots * main_wgs_per_cu(b.precision, tn);
   const int32_t rmax = std::min<int32_t>(b.n_bins, 4096);
   const int32_t step = b.n_bins >= XCDS ? XCDS : 1;
   for (int32_t r = step; r <= rmax; r += step) {
@@ -587,13 +588,13 @@ int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm) {
     const int32_t bins = (b.n_bins + r - 1) / r;
     const int64_t k_span = (int64_t)bins * b.n_fdot;
     const int64_t max_tiles = (k_span + 32 * tm - 1) / (32 * tm) + 1;
-    const int64_t waves = (items + slots - 1) / slots;
+    const int64_t waves = (items + conc - 1) / conc;
     const double cost = (double)waves * (double)max_tiles + 0.02 * (double)waves;
     if (cost < best_cost * 0.999) {
       best_cost = cost;
       best_r = r;
     }
-    if (items > 64LL * slots) break;
+    if (items > 64LL * conc) break;
   }
   return best_r;
 }
@@ -657,7 +658,7 @@ TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s,
   hdr->n_segs = n;
   hdr->total_tiles = tiles;
   hdr->n_ranges = b.precision == P_FFT ? plan_fft_ranges(b, tiles, slots)
-                                       : plan_ranges(b, tiles, slots, sp.tm);
+                                       : plan_ranges(b, tiles, slots, sp.tm, sp.tn);
   hdr->n_items = tiles * hdr->n_ranges;
   ti.n_items = hdr->n_items;
   return ti;
@@ -1066,7 +1067,7 @@ bf_status bf_plan(const bf_bank* bank, const int64_t* n, int32_t n_segs, int32_t
   int32_t tm = 0, tn = 0, pp = 0;
   choose_tile(bank->dev.precision, MODE_SEARCH, &tm, &tn, &pp);
   const int32_t r = bank->dev.precision == P_FFT ? plan_fft_ranges(bank->dev, tiles, slots)
-                                                 : plan_ranges(bank->dev, tiles, slots, tm);
+                                                 : plan_ranges(bank->dev, tiles, slots, tm, tn);
   if (n_ranges) *n_ranges = r;
   if (n_items) *n_items = tiles * r;
   return BF_OK;

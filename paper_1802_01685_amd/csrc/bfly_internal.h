@@ -65,6 +65,12 @@ constexpr float F6_STRIP_LIM = 15360.0f;
 constexpr int chunk_taps(int precision) {
   return precision == P_FP8 ? KCH_FP8 : (precision == P_F16F8 || precision == P_F16F6) ? KCH_F16F8 : KCH;
 }
+// Work-groups of k_main a CU holds, by form and offset blocks per wave: FP8's 2 x 4 tile fits
+// twice (128 accumulators and one strip-fragment buffer in 256 registers, 20 KB of LDS at
+// L = 2000).
+constexpr int main_wgs_per_cu(int precision, int tn) {
+  return precision == P_FP8 && tn <= 4 ? 2 : 1;
+}
 // The fp16 + low-precision residual forms (F16F8, F16F6).
 constexpr bool is_f16r(int precision) { return precision == P_F16F8 || precision == P_F16F6; }
 // Forms whose bank carries per-template exponents and template sums.
@@ -280,7 +286,7 @@ int pred_points(const BankDev& b);
 bool fft_onepass_available(const BankDev& b);
 // Work-groups of the bank's contraction kernel that are resident on one CU (the grid of a
 // persistent launch is the CU count times this).
-int contraction_wgs_per_cu(const BankDev& b);
+int contraction_wgs_per_cu(const BankDev& b, int tn);
 hipError_t launch_fft_pair_list(const BatchHdr* hdr, int32_t seg_slots, const BankDev& b,
                                 hipStream_t s);
 hipError_t launch_fft_pairs(const BatchHdr* hdr, int32_t seg_slots, const BankDev& b,

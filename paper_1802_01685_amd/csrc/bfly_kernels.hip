@@ -1283,7 +1283,7 @@ __device__ __forceinline__ void main_item(const BatchHdr* __restrict__ hdr, int6
         BFLY_INTERLEAVE(false);
       }
 #undef BFLY_INTERLEAVE
-    } else if constexpr (NB <= 4) {
+    } else if constexpr (NB <= 4 && PREC != P_FP8) {
       // Two strip-fragment buffers: chunk c+1's fragments load while chunk c's MFMAs run.
       BFrag<PREC, NB> b0, b1;
       AFrag<PREC, MB> a0, a1;
@@ -1582,7 +1582,7 @@ __device__ __forceinline__ void main_item(const BatchHdr* __restrict__ hdr, int6
 // work-group for a plain batch launch, a persistent loop for captured launches whose grid
 // is fixed while the batch changes.
 template <int PREC, int MB, int NB, int PIPE, int MODE>
-__global__ __launch_bounds__(WG_THREADS, 1) void k_main(const BatchHdr* __restrict__ hdr,
+__global__ __launch_bounds__(WG_THREADS, main_wgs_per_cu(PREC, NB)) void k_main(const BatchHdr* __restrict__ hdr,
                                                         BankDev b, SearchDev p) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int64_t n_items = hdr->n_items;

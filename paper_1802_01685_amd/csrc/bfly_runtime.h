@@ -75,7 +75,7 @@ bf_status check_params(const bf_search_params* p);
 SearchDev make_search(const BankDev& b, const bf_search_params* p, int mode = MODE_SEARCH,
                       float kappa = 0.0f);
 bf_status device_slots(int* slots);
-int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm);
+int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, int tn);
 int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots);
 // FFT form: overlap-save blocks of a series with W offsets.
 inline int64_t fft_blocks(const BankDev& b, int64_t W) {

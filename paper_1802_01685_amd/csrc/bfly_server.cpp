@@ -406,7 +406,7 @@ bf_status bf_server_create(const bf_bank* bank, const bf_server_desc* desc, bf_s
       bf_status kst = ce == hipSuccess
                           ? enqueue_kernels(bank->dev, s->sp, t.table_dev, desc->max_slots,
                                             s->x_blocks, s->x_blocks * (int64_t)2048,
-                                            (int64_t)s->slots * contraction_wgs_per_cu(bank->dev),
+                                            (int64_t)s->slots * contraction_wgs_per_cu(bank->dev, s->sp.tn),
                                             t.stream, nullptr)
                           : hip_error(ce, "hipMemcpyAsync(capture)");
       e = hipStreamEndCapture(t.stream, &t.graph);
