@@ -231,7 +231,8 @@ double env_double(const char* name, double dflt) {
 // wave, and the K-loop schedule.  BF_TILE=<tm>x<tn>[i|p] (e.g. "2x8i"; i = interleaved,
 // p = pair streaming) overrides the default -- a tuning knob for experiments; FP32 and BF16 results do not
 // depend on it (FP8 does, through its per-strip scales).
-void choose_tile(int precision, int mode, int32_t* tm, int32_t* tn, int32_t* pipe) {
+// Returns whether the override applies.
+bool choose_tile(int precision, int mode, int32_t* tm, int32_t* tn, int32_t* pipe) {
   // Defaults from measurement on MI355X: the split forms are fastest with 2 x 8 blocks and
   // the interleaved schedule; FP32 (64-cycle MFMAs) and FP8 with 2 x 4.
   // F16F8 and F16F6 have one shape, 2 x 8 with their pair-streaming schedule.
@@ -249,8 +250,10 @@ void choose_tile(int precision, int mode, int32_t* tm, int32_t* tn, int32_t* pip
       *tm = a;
       *tn = c;
       *pipe = pp;
+      return true;
     }
   }
+  return false;
 }
 
 // Per-thread pool of timing records, collected by bf_kernel_times.  The events live until
@@ -333,7 +336,10 @@ bf_status run_batch(const bf_bank* bank, const bf_segment* segs, int32_t n_segs,
   const int pass_mode = !with_tails ? MODE_SEARCH
                         : b.precision == P_FFT ? (onepass ? MODE_ONEPASS : MODE_SEARCH)
                                                : MODE_SIGMA;
-  const SearchDev sp = make_search(b, prm, pass_mode, kappa);
+  int slots = 0;
+  if ((st = device_slots(&slots)) != BF_OK) return st;
+  SearchDev sp = make_search(b, prm, pass_mode, kappa);
+  fit_tile(b, segs, n_segs, slots, &sp);
   SeriesBufs one;                 // a single series needs no host allocation
   std::vector<SeriesBufs> many;
   if (n_segs > 1) many.resize((size_t)n_segs);
@@ -355,8 +361,6 @@ bf_status run_batch(const bf_bank* bank, const bf_segment* segs, int32_t n_segs,
       if (cap >= 0 && cap < q.cand_cap) q.cand_cap = cap;
     }
   }
-  int slots = 0;
-  if ((st = device_slots(&slots)) != BF_OK) return st;
 
   BatchHdr* tab_dev = (BatchHdr*)ws;
   TableInfo ti;
@@ -575,7 +579,8 @@ int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots) {
 }
 
 constexpr int XCDS = 8;
-int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, int tn) {
+int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, int tn,
+                    double* makespan) {
   double best_cost = 1e300;
   int32_t best_r = 1;
   const int64_t conc = (int64_t)slots * main_wgs_per_cu(b.precision, tn);
@@ -596,7 +601,36 @@ int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, in
     }
     if (items > 64LL * conc) break;
   }
+  if (makespan) *makespan = best_cost;
   return best_r;
+}
+
+// A search too small for the default tile: FP32's 1 x 1 tile (128 offsets per work-group, 32
+// templates at a time) where it shortens the longest CU's work, in accumulator blocks, by a
+// tenth or more.  At 4 s of 512 Hz against a 16 x 16 bank the 2 x 4 tile makes 32 work items of
+// one 64-template tile each and the search takes 75 us in k_main, a quarter of the chip one
+// block after another; the 1 x 1 tile makes 104 items an eighth as long (14 us).  From a few
+// items per CU on the two tie and the 2 x 4 tile, which reads each fragment fewer times, stays.
+// The results do not depend on the shape in FP32.  (The other forms' strips carry scales or
+// schedules tied to their tile and stay as they are.)
+void fit_tile(const BankDev& b, const bf_segment* segs, int32_t n_segs, int slots,
+              SearchDev* sp) {
+  int32_t tm, tn, pipe;
+  if (b.precision != P_FP32 || sp->mode != MODE_SEARCH ||
+      choose_tile(b.precision, sp->mode, &tm, &tn, &pipe))
+    return;
+  const auto cost = [&](int m, int n) {
+    const int64_t n_wg = 32 * n * WG_WAVES;
+    int64_t tiles = 0;
+    for (int32_t i = 0; i < n_segs; ++i) tiles += (segs[i].n - b.L + 1 + n_wg - 1) / n_wg;
+    double c = 0.0;
+    plan_ranges(b, tiles, slots, m, n, &c);
+    return c * m * n;
+  };
+  if (cost(1, 1) < 0.9 * cost(sp->tm, sp->tn)) {
+    sp->tm = sp->tn = 1;
+    sp->n_wg = 32 * WG_WAVES;
+  }
 }
 
 TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s, int32_t n,
@@ -1053,23 +1087,28 @@ bf_status bf_plan(const bf_bank* bank, const int64_t* n, int32_t n_segs, int32_t
                   int64_t* n_items) {
   if (!bank || !n || n_segs < 1) return fail(BF_EINVAL, "bad arguments");
   int64_t tiles = 0;
-  for (int32_t i = 0; i < n_segs; ++i) {
-    if (n[i] < bank->dev.L) return fail(BF_EINVAL, "series shorter than L");
-    int32_t tm = 0, tn = 0, pp = 0;
-    choose_tile(bank->dev.precision, MODE_SEARCH, &tm, &tn, &pp);
-    const int64_t n_wg = bank->dev.precision == P_FFT ? 2 * (int64_t)bank->dev.fft_m - bank->dev.L + 1
-                                                       : 32 * (int64_t)tn * WG_WAVES;
-    tiles += (n[i] - bank->dev.L + 1 + n_wg - 1) / n_wg;
-  }
   int slots = 0;
   bf_status st = device_slots(&slots);
   if (st != BF_OK) return st;
-  int32_t tm = 0, tn = 0, pp = 0;
-  choose_tile(bank->dev.precision, MODE_SEARCH, &tm, &tn, &pp);
-  const int32_t r = bank->dev.precision == P_FFT ? plan_fft_ranges(bank->dev, tiles, slots)
-                                                 : plan_ranges(bank->dev, tiles, slots, tm, tn);
-  if (n_ranges) *n_ranges = r;
-  if (n_items) *n_items = tiles * r;
+  try {
+    std::vector<bf_segment> segs((size_t)n_segs);
+    for (int32_t i = 0; i < n_segs; ++i) {
+      if (n[i] < bank->dev.L) return fail(BF_EINVAL, "series shorter than L");
+      segs[(size_t)i].n = n[i];
+    }
+    const bf_search_params prm = {BF_NORM_CENTRED, 1, 1, 0, 0.0, 1.0};
+    SearchDev sp = make_search(bank->dev, &prm, MODE_SEARCH);
+    fit_tile(bank->dev, segs.data(), n_segs, slots, &sp);
+    for (int32_t i = 0; i < n_segs; ++i)
+      tiles += (n[i] - bank->dev.L + 1 + sp.n_wg - 1) / sp.n_wg;
+    const int32_t r = bank->dev.precision == P_FFT
+                          ? plan_fft_ranges(bank->dev, tiles, slots)
+                          : plan_ranges(bank->dev, tiles, slots, sp.tm, sp.tn);
+    if (n_ranges) *n_ranges = r;
+    if (n_items) *n_items = tiles * r;
+  } catch (...) {
+    return fail(BF_ENOMEM, "internal error");
+  }
   return BF_OK;
 }
 

@@ -910,6 +910,10 @@ __device__ __forceinline__ void flush_bin(const SegDesc& sg, const BankDev& b,
   if (lane == 0 && fix != 0ull) atomicAdd(sg.spec_acc + bin, fix);
 }
 
+template <int V>
+struct IntC {
+  static constexpr int value = V;
+};
 template <bool B>
 struct BoolC {
   static constexpr bool value = B;
@@ -1283,6 +1287,34 @@ __device__ __forceinline__ void main_item(const BatchHdr* __restrict__ hdr, int6
         BFLY_INTERLEAVE(false);
       }
 #undef BFLY_INTERLEAVE
+    } else if constexpr (MB * NB == 1) {
+      // One accumulator block: a chunk's MFMAs last 512 cycles (FP32), less than the L2's
+      // latency under load, so the template fragments are loaded three chunks ahead.
+      constexpr int AHEAD = 3;
+      AFrag<PREC, MB> a[AHEAD + 1];
+      BFrag<PREC, NB> bb[2];
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i)
+        load_a<PREC, MB>(a[i], b.data, blk0, i < nc ? i : nc - 1, nc, lane);
+      load_b<PREC, NB>(bb[0], lds, off_w, 0, n, h, plane_bytes);
+      __builtin_amdgcn_sched_barrier(0);
+      auto chunk = [&](auto slot, int c) {
+        constexpr int s = decltype(slot)::value;
+        load_a<PREC, MB>(a[(s + AHEAD) & 3], b.data, blk0, c + AHEAD < nc ? c + AHEAD : nc - 1, nc,
+                         lane);
+        load_b<PREC, NB>(bb[(s + 1) & 1], lds, off_w, c + 1 < nc ? c + 1 : c, n, h, plane_bytes);
+        __builtin_amdgcn_sched_barrier(0);
+        mma_chunk<PREC, MB, NB>(acc, a[s], bb[s & 1], sa, sb);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      for (int c = 0; c < nc; c += 4) {   // n_chunks is even
+        chunk(IntC<0>{}, c);
+        chunk(IntC<1>{}, c + 1);
+        if (c + 2 < nc) {
+          chunk(IntC<2>{}, c + 2);
+          chunk(IntC<3>{}, c + 3);
+        }
+      }
     } else if constexpr (NB <= 4 && PREC != P_FP8) {
       // Two strip-fragment buffers: chunk c+1's fragments load while chunk c's MFMAs run.
       BFrag<PREC, NB> b0, b1;
@@ -1640,6 +1672,7 @@ static hipError_t launch_main_t(const BatchHdr* hdr, int64_t blocks, const BankD
     if (b.precision == P_FP32) {                                                       \
       if (v_ == 0x024) return FN<P_FP32, 2, 4, 0, MODE_SEARCH>(__VA_ARGS__);           \
       if (v_ == 0x018) return FN<P_FP32, 1, 8, 0, MODE_SEARCH>(__VA_ARGS__);           \
+      if (v_ == 0x011) return FN<P_FP32, 1, 1, 0, MODE_SEARCH>(__VA_ARGS__);           \
     } else if (b.precision == P_BF16X3) {                                              \
       if (v_ == 0x024) return FN<P_BF16X3, 2, 4, 0, MODE_SEARCH>(__VA_ARGS__);         \
       if (v_ == 0x018) return FN<P_BF16X3, 1, 8, 0, MODE_SEARCH>(__VA_ARGS__);         \
@@ -1671,7 +1704,7 @@ bool main_variant_exists(int precision, int tm, int tn, int pipe, int mode) {
     return v == 0x024 || v == 0x018 || v == 0x028 || v == 0x124 || v == 0x128;
   if (precision == P_FP8) return v == 0x024 || v == 0x018 || v == 0x128;
   if (precision == P_F16X2) return v == 0x024 || v == 0x028 || v == 0x128;
-  return v == 0x024 || v == 0x018;
+  return v == 0x024 || v == 0x018 || v == 0x011;
 }
 
 // Sets the kernel's dynamic-LDS limit; call before launching (and before capturing).
