@@ -300,17 +300,20 @@ __device__ __forceinline__ double block_sum_d(double v, double* red) {
   return t;
 }
 
-// Bank spectra: one work-group per template builds the zero-mean unit-norm template in
-// float64, rounds it to float32 and stores its real-FFT spectrum (row stride M + 2).
+// Stages template k (zero mean, unit norm, float64, rounded to float32; zero for padding
+// templates and past its L taps) as z[n] = (h[2n], h[2n + 1]) in buf, taps past 2M added onto
+// the first ones.  Each thread forms its samples once (n = t + T i, at most 16 within the
+// transform) and keeps them for the mean, the norm and the staging: one float64 cosine per
+// sample is most of a bank's creation (65,536 x 4096: 3.1 ms with three, 1.6 ms with one).
+// Returns false for a template whose centred norm vanishes.
 template <int M>
-__global__ __launch_bounds__(Plan<M>::T) void k_fft_bank(GridDev g, BankDev b,
-                                                          float2* spectra, unsigned int* bad) {
+__device__ __forceinline__ bool stage_template(const GridDev& g, const BankDev& b, int64_t k,
+                                               float2* buf, double* red) {
   constexpr int T = Plan<M>::T;
-  __shared__ float2 buf[Padded<M>::n];
-  __shared__ double red[T / 64];
-  const int64_t k = blockIdx.x;
+  constexpr int NS = 2 * M / T;
   const bool real = k < b.K;
-  double f0 = 0.0, fdot = 0.0, mu = 0.0, nrm = 1.0;
+  double s[NS], f0 = 0.0, fdot = 0.0, mu = 0.0, nrm = 1.0;
+  bool good = true;
   if (real) {
     const int64_t il = k / g.n_fdot;
     const int j = (int)(k % g.n_fdot);
@@ -319,28 +322,54 @@ __global__ __launch_bounds__(Plan<M>::T) void k_fft_bank(GridDev g, BankDev b,
     fdot = (g.n_fdot > 1 && j == g.n_fdot - 1) ? g.fdot_max
                                                : (double)j * g.fdot_step + g.fdot_min;
     double s1 = 0.0;
-    for (int n = threadIdx.x; n < b.L; n += T) s1 += template_sample(g.fs, f0, fdot, n);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const int n = threadIdx.x + T * i;
+      if (n < b.L) {
+        s[i] = template_sample(g.fs, f0, fdot, n);
+        s1 += s[i];
+      }
+    }
+    for (int n = 2 * M + threadIdx.x; n < b.L; n += T) s1 += template_sample(g.fs, f0, fdot, n);
     mu = block_sum_d<T / 64>(s1, red) / (double)b.L;
     double s2 = 0.0;
-    for (int n = threadIdx.x; n < b.L; n += T) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      if (threadIdx.x + T * i < b.L) {
+        const double v = s[i] - mu;
+        s2 += v * v;
+      }
+    }
+    for (int n = 2 * M + threadIdx.x; n < b.L; n += T) {
       const double v = template_sample(g.fs, f0, fdot, n) - mu;
       s2 += v * v;
     }
     s2 = block_sum_d<T / 64>(s2, red);
-    nrm = sqrt(s2);
-    if (!(s2 > 1e-18 * (double)b.L)) {
-      if (threadIdx.x == 0) atomicAdd(bad, 1u);
-      nrm = 1.0;
-    }
+    good = s2 > 1e-18 * (double)b.L;
+    nrm = s2 > 0.0 ? sqrt(s2) : 1.0;
   }
-  for (int n = threadIdx.x; n < M; n += T) {
-    float2 z = make_float2(0.0f, 0.0f);
-    if (real && 2 * n < b.L) z.x = (float)((template_sample(g.fs, f0, fdot, 2 * n) - mu) / nrm);
-    if (real && 2 * n + 1 < b.L)
-      z.y = (float)((template_sample(g.fs, f0, fdot, 2 * n + 1) - mu) / nrm);
-    buf[pad(n)] = z;
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    const int n = threadIdx.x + T * i;
+    float z = 0.0f;
+    if (real && n < b.L) z += (float)((s[i] - mu) / nrm);
+    for (int q = n + 2 * M; q < b.L && real; q += 2 * M)
+      z += (float)((template_sample(g.fs, f0, fdot, q) - mu) / nrm);
+    ((float*)(buf + pad(n >> 1)))[n & 1] = z;
   }
   __syncthreads();
+  return good;
+}
+
+// Bank spectra: one work-group per template builds it and stores its real-FFT spectrum (row
+// stride M + 2).
+template <int M>
+__global__ __launch_bounds__(Plan<M>::T) void k_fft_bank(GridDev g, BankDev b,
+                                                          float2* spectra, unsigned int* bad) {
+  __shared__ float2 buf[Padded<M>::n];
+  __shared__ double red[Plan<M>::T / 64];
+  const int64_t k = blockIdx.x;
+  if (!stage_template<M>(g, b, k, buf, red) && threadIdx.x == 0) atomicAdd(bad, 1u);
   rfft_post<M>(buf, spectra + k * (int64_t)(M + 2));
 }
 
@@ -434,36 +463,7 @@ __global__ __launch_bounds__(Plan<M>::T) void k_pred_gen(const BatchHdr* __restr
   __shared__ float2 buf[Padded<M>::n];
   __shared__ double red[T / 64];
   const int64_t k = blockIdx.x;
-  const bool real = k < b.K;
-  double f0 = 0.0, fdot = 0.0, mu = 0.0, nrm = 1.0;
-  if (real) {
-    const int64_t il = k / g.n_fdot;
-    const int j = (int)(k % g.n_fdot);
-    const int64_t ig = g.f0_lo + il;
-    f0 = (g.n_f0 > 1 && ig == g.n_f0 - 1) ? g.f0_max : (double)ig * g.f0_step + g.f0_min;
-    fdot = (g.n_fdot > 1 && j == g.n_fdot - 1) ? g.fdot_max
-                                               : (double)j * g.fdot_step + g.fdot_min;
-    double s1 = 0.0;
-    for (int n = threadIdx.x; n < b.L; n += T) s1 += template_sample(g.fs, f0, fdot, n);
-    mu = block_sum_d<T / 64>(s1, red) / (double)b.L;
-    double s2 = 0.0;
-    for (int n = threadIdx.x; n < b.L; n += T) {
-      const double v = template_sample(g.fs, f0, fdot, n) - mu;
-      s2 += v * v;
-    }
-    s2 = block_sum_d<T / 64>(s2, red);
-    nrm = s2 > 0.0 ? sqrt(s2) : 1.0;
-  }
-  // taps past 2M alias onto the transform (only when L > 2M; a prediction, checked later)
-  for (int n = threadIdx.x; n < M; n += T) {
-    float2 z = make_float2(0.0f, 0.0f);
-    for (int q = 2 * n; q < b.L && real; q += 2 * M) {
-      z.x += (float)((template_sample(g.fs, f0, fdot, q) - mu) / nrm);
-      if (q + 1 < b.L) z.y += (float)((template_sample(g.fs, f0, fdot, q + 1) - mu) / nrm);
-    }
-    buf[pad(n)] = z;
-  }
-  __syncthreads();
+  (void)stage_template<M>(g, b, k, buf, red);   // taps past 2M (L > 2M) only alias a prediction
   float2 out[8];
   PassTw<M, false> tw;
   tw.init();
