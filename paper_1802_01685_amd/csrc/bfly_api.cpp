@@ -366,13 +366,13 @@ bf_status run_batch(const bf_bank* bank, const bf_segment* segs, int32_t n_segs,
   TableInfo ti;
   if (upload == TableUpload::Kernel) {
     OneSeriesTable tab;
-    ti = fill_table(b, sp, sb, 1, slots, &tab.hdr);
+    ti = fill_table(b, sp, sb, 1, slots, &tab.hdr, !with_tails);
     HIP_TRY(launch_put_table(tab, (OneSeriesTable*)tab_dev, stream), "k_put_table launch");
   } else {
     Staging* stg = acquire_staging(table_bytes(n_segs), dev, &st);
     if (!stg) return st;
     BatchHdr* hdr = (BatchHdr*)stg->host;
-    ti = fill_table(b, sp, sb, n_segs, slots, hdr);
+    ti = fill_table(b, sp, sb, n_segs, slots, hdr, !with_tails);
     hipError_t e =
         hipMemcpyAsync(tab_dev, hdr, table_bytes(n_segs), hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) {
@@ -391,7 +391,9 @@ bf_status run_batch(const bf_bank* bank, const bf_segment* segs, int32_t n_segs,
     return st;
   const int32_t xb =
       (int32_t)std::min<int64_t>(std::max<int64_t>((ti.max_words + 255) / 256, 1), 2048);
-  if (!with_tails) return enqueue_kernels(b, sp, tab_dev, n_segs, xb, ti.max_n, ti.n_items, stream, te);
+  if (!with_tails)
+    return enqueue_kernels(b, sp, tab_dev, n_segs, xb, ti.max_n, ti.n_items, stream, te,
+                           ti.split);
   SearchDev sp_t = sp;
   sp_t.mode = MODE_TAILS;
   if (b.precision != P_FFT) HIP_TRY(prepare_main(b, sp_t), "hipFuncSetAttribute(k_main)");
@@ -543,24 +545,36 @@ bf_status device_slots(int* slots) {
 // multiple of 8, so that each XCD sweeps its own ranges (see the item order in k_main).
 // FFT form: items = blocks x ranges of whole f0 bins; two work-groups fit a CU.  Minimises
 // waves x (bins per range), preferring fewer ranges (each item transforms its block once).
+// The N = 8192 kernel deals each XCD whole ranges when their count is a multiple of 8, so its
+// plan counts one XCD's items on its 64 work-groups.
+//
+// Cost of a plan of k_fft4k / k_fft4k_search in templates: an item's set-up and bin end take
+// about as long as 6 templates, and of two work-groups on a CU the older one's waves win the
+// issue slots (2.65 against 3.8 us per template), so the younger one's last item runs on alone:
+// about 0.3 of an item where work-groups take several, 0.1 in a single round.  Short items
+// therefore pay until their set-up shows: 65,536 x 4096 on 31 blocks takes 12.6 ms with 16
+// ranges, 11.9 with 128 and 11.3 with 256; 720,000 x 2000 on 42 blocks 178 ms with 24 and
+// 170 ms with 240.
+double fft4k_cost(int64_t items_per_xcd, int64_t per_xcd, int64_t templates) {
+  const double len = (double)templates, n = (double)items_per_xcd;
+  return items_per_xcd <= per_xcd ? 1.1 * len + 6.0 : n * (len + 6.0) / (double)per_xcd + 0.3 * len;
+}
+
 int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots) {
   double best_cost = 1e300;
   int32_t best_r = 1;
   const int64_t conc = 2 * (int64_t)slots;
   if (b.fft_m == 4096 && b.n_bins >= 8) {
-    // The N = 8192 kernel (two work-groups per CU) deals each XCD whole ranges when their
-    // count is a multiple of 8: cost = the XCD's rounds of items x bins per range.
-    const int64_t per_xcd = conc / 8;
     for (int32_t r = 8; r <= b.n_bins; r += 8) {
       const int64_t items = total_tiles * r;
       if (items > (int64_t)0x7FFFFFFF) break;
-      const int64_t rounds = (total_tiles * (r / 8) + per_xcd - 1) / per_xcd;
-      const double cost = (double)rounds * (double)((b.n_bins + r - 1) / r) + 0.01 * (double)rounds;
+      const double cost = fft4k_cost(total_tiles * (r / 8), conc / 8,
+                                     (int64_t)((b.n_bins + r - 1) / r) * b.n_fdot);
       if (cost < best_cost * 0.999) {
         best_cost = cost;
         best_r = r;
       }
-      if (items > 16 * conc) break;
+      if (items > 64 * conc) break;
     }
     return best_r;
   }
@@ -576,6 +590,30 @@ int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots) {
     if (items > 16 * conc) break;
   }
   return best_r;
+}
+
+// Ranges of whole bins leave CUs idle when a search has few of them.  k_fft4k_search also takes
+// ranges of templates that cut bins: a multiple of 8, so that each XCD sweeps its own ranges in
+// step and shares their spectra through its L2, as many as fill the XCD's 64 work-groups q
+// times.  Taken where fft4k_cost falls by a twentieth and by k_bin_sums' 15 us, about 5
+// templates.  7 blocks against 48 bins of 200 templates: 336 items of 200 templates or 504 of
+// 133, 0.71 and 0.50 ms in the kernel.  Returns the ranges, 0 for whole bins.
+int32_t plan_split_ranges(const BankDev& b, int64_t total_tiles, int slots, int32_t n_ranges) {
+  const int64_t per_xcd = 2 * (int64_t)slots / 8;
+  const double whole = fft4k_cost((total_tiles * n_ranges + 7) / 8, per_xcd,
+                                  (int64_t)((b.n_bins + n_ranges - 1) / n_ranges) * b.n_fdot);
+  int32_t best = 0;
+  double best_cost = 0.95 * whole - 5.0;
+  for (int q = 1; q <= 4; ++q) {
+    const int64_t r = 8 * (q * per_xcd / total_tiles);
+    if (r < 8 || r > b.K) continue;
+    const double c = fft4k_cost(total_tiles * (r / 8), per_xcd, (b.K + r - 1) / r);
+    if (c < best_cost) {
+      best_cost = c;
+      best = (int32_t)r;
+    }
+  }
+  return best;
 }
 
 constexpr int XCDS = 8;
@@ -634,8 +672,9 @@ void fit_tile(const BankDev& b, const bf_segment* segs, int32_t n_segs, int slot
 }
 
 TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s, int32_t n,
-                     int slots, BatchHdr* hdr) {
+                     int slots, BatchHdr* hdr, bool may_split) {
   TableInfo ti;
+  bool all_spec = true;
   SegDesc* tab = (SegDesc*)(hdr + 1);
   int64_t tiles = 0;
   for (int32_t i = 0; i < n; ++i) {
@@ -654,6 +693,7 @@ TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s,
     d.max_abs = s[i].out.max_abs;
     d.argmax = s[i].out.argmax;
     d.spec = s[i].out.spec;
+    all_spec = all_spec && d.spec;
     d.spectrum = s[i].out.spectrum;
     d.hist = s[i].out.hist;
     d.n_degenerate = s[i].out.n_degenerate;
@@ -693,6 +733,14 @@ TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s,
   hdr->total_tiles = tiles;
   hdr->n_ranges = b.precision == P_FFT ? plan_fft_ranges(b, tiles, slots)
                                        : plan_ranges(b, tiles, slots, sp.tm, sp.tn);
+  if (b.precision == P_FFT && may_split && all_spec && fft_can_split_bins(b, sp)) {
+    const int32_t r = plan_split_ranges(b, tiles, slots, hdr->n_ranges);
+    if (r > 0) {
+      hdr->n_ranges = r;
+      hdr->split = 1;
+      ti.split = true;
+    }
+  }
   hdr->n_items = tiles * hdr->n_ranges;
   ti.n_items = hdr->n_items;
   return ti;
@@ -727,7 +775,8 @@ TimingSet* timing_slot(int dev, bf_status* st) {
 // main_blocks: work-groups of the contraction kernel (n_items for one item each).
 bf_status enqueue_kernels(const BankDev& b, const SearchDev& sp, const BatchHdr* table_dev,
                           int32_t seg_slots, int32_t x_blocks, int64_t max_n,
-                          int64_t main_blocks, hipStream_t stream, TimingSet* te) {
+                          int64_t main_blocks, hipStream_t stream, TimingSet* te,
+                          bool split) {
   const int32_t xb = x_blocks > 0 ? x_blocks : 1;
   if (te) HIP_TRY(hipEventRecord(te->ev[0], stream), "hipEventRecord");
   HIP_TRY(launch_zero(table_dev, seg_slots, xb, b, sp, stream), "k_zero launch");
@@ -740,6 +789,8 @@ bf_status enqueue_kernels(const BankDev& b, const SearchDev& sp, const BatchHdr*
     HIP_TRY(launch_fft_search(table_dev, main_blocks, b, sp, stream), "k_fft launch");
   else
     HIP_TRY(launch_main(table_dev, main_blocks, b, sp, stream), "k_main launch");
+  if (split)
+    HIP_TRY(launch_bin_sums(table_dev, seg_slots, max_n, b, stream), "k_bin_sums launch");
   if (te) HIP_TRY(hipEventRecord(te->ev[4], stream), "hipEventRecord");
   HIP_TRY(launch_finalize(table_dev, seg_slots, xb, b, sp, stream), "k_finalize launch");
   if (te) HIP_TRY(hipEventRecord(te->ev[5], stream), "hipEventRecord");

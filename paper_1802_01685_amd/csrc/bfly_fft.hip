@@ -1312,10 +1312,12 @@ __global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restr
   constexpr int BUF = M + M / 32;
   __shared__ float2 lds[2 * BUF];
   __shared__ float2 tab3[7 * 64];
+  __shared__ uint32_t taken;
   const SegDesc* segs = hdr_segs(hdr);
   const float2* spectra = (const float2*)b.data;
   const int n_ranges = hdr->n_ranges;
   const int64_t n_items = hdr->n_items;
+  const bool split = hdr->split != 0;
   const int valid = 2 * M - b.L + 1;
   const int t = threadIdx.x;
   const int lane = t & 63;
@@ -1360,7 +1362,12 @@ __global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restr
   const int w3 = 512 * wave + lane;              // and writes 512 wave + lane + 64 r
 
   const int64_t total_tiles = hdr->total_tiles;
-  for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+  // A batch launch has a work-group per item.  A launch with a fixed grid takes further items
+  // from a counter per XCD (item mod 8 keeps the XCD): the older of two work-groups on a CU runs
+  // faster, so equal shares would leave the others behind.
+  const bool dealt = gridDim.x % 8 == 0;
+  int64_t item = blockIdx.x;
+  while (item < n_items) {
     int rg;
     int64_t tt;
     if (n_ranges % 8 == 0) {
@@ -1379,8 +1386,11 @@ __global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restr
     const SegDesc& sg = segs[lo];
     const int64_t blk = tt - sg.tile0;
     const int tau_base = (int)(blk * valid);     // series are shorter than 2^31 samples
-    const int b_lo = (int)((int64_t)rg * b.n_bins / n_ranges);
-    const int b_hi = (int)((int64_t)(rg + 1) * b.n_bins / n_ranges);
+    // the templates of the range
+    const int64_t units = split ? b.K : b.n_bins;
+    const int per = split ? 1 : nfd;
+    const int k_lo = __builtin_amdgcn_readfirstlane((int)(rg * units / n_ranges) * per);
+    const int k_hi = __builtin_amdgcn_readfirstlane((int)((rg + 1) * units / n_ranges) * per);
     const float2* xsrc = sg.xspec + blk * (int64_t)(M + 2);
     float2 x[8];
     {
@@ -1397,7 +1407,6 @@ __global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restr
     double best[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o) best[o] = 0.0;
-    const int k_lo = b_lo * nfd, k_hi = b_hi * nfd;
     float2 h[8], h2;
     auto load_h = [&](int k) {
       const __amdgpu_buffer_rsrc_t hr = row_rsrc(spectra + (int64_t)k * (M + 2));
@@ -1514,12 +1523,14 @@ __global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restr
       if constexpr (RMAX > 7) keep(IntC<6>{});
       if (last) keep(IntC<RMAX - 1>{});
     };
-    for (int bin = b_lo; bin < b_hi; ++bin) {
-      const int k_end = (bin + 1) * nfd;
-      for (int k = bin * nfd; k < k_end; k += 2) {
+    int bin = __builtin_amdgcn_readfirstlane(k_lo / nfd);
+    for (int k0 = k_lo; k0 < k_hi; ++bin) {
+      const int k_end = min((bin + 1) * nfd, k_hi);
+      for (int k = k0; k < k_end; k += 2) {
         step(IntC<0>{}, k);
         if (k + 1 < k_end) step(IntC<1>{}, k + 1);
       }
+      k0 = k_end;
       __syncthreads();   // the next bin (or item) starts on parity 0 again
       // end of bin: spectrogram row, spectrum sum, packed per-offset maxima
       unsigned long long fix = 0ull;
@@ -1536,7 +1547,7 @@ __global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restr
             if (sg.spec) {
               const int row = p.t_block == 1 ? tau : tau / p.t_block;
               const int64_t at = (int64_t)bin * sg.spec_rows + row;
-              if (p.t_block == 1)
+              if (p.t_block == 1 && !split)
                 sg.spec[at] = s;
               else
                 atomicMax((unsigned int*)sg.spec + at, __float_as_uint(s));
@@ -1549,10 +1560,37 @@ __global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restr
         best[o] = 0.0;
         __builtin_amdgcn_sched_barrier(0);
       }
-      fix = wave_sum_u64(fix);
-      if ((t & 63) == 0 && fix != 0ull) atomicAdd(sg.spec_acc + bin, fix);
+      if (!split) {   // else k_bin_sums, once the parts of every bin have met
+        fix = wave_sum_u64(fix);
+        if ((t & 63) == 0 && fix != 0ull) atomicAdd(sg.spec_acc + bin, fix);
+      }
+    }
+    if (gridDim.x >= n_items) break;
+    if (dealt) {
+      if (t == 0) taken = atomicAdd(const_cast<uint32_t*>(hdr->next) + (blockIdx.x & 7), 1u);
+      __syncthreads();
+      item = (int64_t)gridDim.x + 8 * (int64_t)taken + (blockIdx.x & 7);
+      __syncthreads();   // all have read it
+    } else {
+      item += gridDim.x;
     }
   }
+}
+
+// The spectrum sums of a search whose ranges cut bins, from the spectrogram (t_block = 1; entries
+// of degenerate windows are 0 and add nothing): the same fixed-point terms as at a bin's end.
+// grid = (blocks over the offsets, bins, series).
+__global__ __launch_bounds__(256) void k_bin_sums(const BatchHdr* __restrict__ hdr) {
+  if ((int)blockIdx.z >= hdr->n_segs) return;
+  const SegDesc& sg = hdr_segs(hdr)[blockIdx.z];
+  const int bin = (int)blockIdx.y;
+  const float* row = sg.spec + (int64_t)bin * sg.spec_rows;
+  unsigned long long fix = 0ull;
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < sg.W; i += stride)
+    fix += (unsigned long long)__double2ll_rn((double)row[i] * SPEC_FIX_SCALE);
+  fix = wave_sum_u64(fix);
+  if ((threadIdx.x & 63) == 0 && fix != 0ull) atomicAdd(sg.spec_acc + bin, fix);
 }
 
 // The tails of the (block, template) pairs the single pass of k_fft4k listed, for every
@@ -1798,6 +1836,19 @@ __global__ __launch_bounds__(256) void k_fft_pair_list(const BatchHdr* __restric
 }
 
 }  // namespace
+
+bool fft_can_split_bins(const BankDev& b, const SearchDev& p) {
+  return b.fft_m == 4096 && fft4k_enabled() && p.mode == MODE_SEARCH && p.t_block == 1 &&
+         b.n_bins <= 65535;
+}
+
+hipError_t launch_bin_sums(const BatchHdr* hdr, int32_t seg_slots, int64_t max_W,
+                           const BankDev& b, hipStream_t s) {
+  const int64_t xb = (max_W + 2047) / 2048;
+  hipLaunchKernelGGL(k_bin_sums, dim3((unsigned)(xb < 1024 ? xb : 1024), (unsigned)b.n_bins, (unsigned)seg_slots),
+                     dim3(256), 0, s, hdr);
+  return hipGetLastError();
+}
 
 hipError_t launch_fft_pair_list(const BatchHdr* hdr, int32_t seg_slots, const BankDev& b,
                                 hipStream_t s) {

@@ -160,10 +160,13 @@ __device__ inline float series_offset(const SegDesc& sg) {
 // largest batch, the contraction kernel looping over its work items) serves any batch.
 struct BatchHdr {
   int32_t n_segs;
-  int32_t n_ranges;     // bin ranges the bank sweep is split into
+  int32_t n_ranges;     // ranges the bank sweep is split into: whole bins, or (split) templates
   int64_t total_tiles;  // sum of n_tiles over the series
   int64_t n_items;      // total_tiles * n_ranges
-  int64_t reserved[5];
+  int32_t split;        // 1: ranges of templates that may cut bins (k_fft4k_search only)
+  int32_t reserved0;
+  uint32_t next[8];     // k_fft4k_search with fewer work-groups than items: items taken per XCD
+                        // beyond the first of each work-group (0 in an uploaded table)
 };
 static_assert(sizeof(BatchHdr) == 64, "BatchHdr layout");
 
@@ -267,6 +270,12 @@ size_t main_lds_bytes(int precision, int L_pad, int n_wg);
 hipError_t launch_fft_bank(const GridDev& g, const BankDev& b, void* dst, hipStream_t s);
 hipError_t launch_fft_search(const BatchHdr* hdr, int64_t blocks, const BankDev& b,
                              const SearchDev& p, hipStream_t s);
+// Spectrum sums of a search whose ranges cut bins, from the finished spectrogram.
+hipError_t launch_bin_sums(const BatchHdr* hdr, int32_t seg_slots, int64_t max_W,
+                           const BankDev& b, hipStream_t s);
+// An FFT search's ranges may cut bins: the N = 8192 kernel runs it, and the spectrogram is kept
+// whole (t_block = 1), where the parts of a bin meet.
+bool fft_can_split_bins(const BankDev& b, const SearchDev& p);
 // The sigma or tails pass of a tail search (p.mode), after the search left the data spectra.
 // Single-pass tail search (bfly_tails.hip, bfly_fft.hip).  The predictor: lag sums of each
 // series' locally normalised samples (k_acf), their cosine transform on pred_n points

@@ -94,9 +94,11 @@ struct TableInfo {
   int64_t max_n = 0;
   int64_t max_words = 0;
   int64_t n_items = 0;
+  bool split = false;   // ranges cut bins: the caller launches k_bin_sums
 };
+// may_split: the ranges of an FFT search may cut bins where its kernel can.
 TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s, int32_t n,
-                     int slots, BatchHdr* hdr);
+                     int slots, BatchHdr* hdr, bool may_split);
 
 // The batch table of a single series, laid out as in the workspace ([BatchHdr][SegDesc]).
 struct OneSeriesTable {
@@ -131,8 +133,8 @@ TimingSet* timing_slot(int device, bf_status* st);
 // prepare_main(b, sp) must have been called once before (outside any stream capture).
 bf_status enqueue_kernels(const BankDev& b, const SearchDev& sp, const BatchHdr* table_dev,
                           int32_t seg_slots, int32_t x_blocks, int64_t max_n,
-                          int64_t main_blocks,
-                          hipStream_t stream, TimingSet* te);
+                          int64_t main_blocks, hipStream_t stream, TimingSet* te,
+                          bool split = false);
 // The tail search: the kernels above with the contraction in MODE_SIGMA, then k_sigma and
 // the MODE_TAILS contraction (sp_sigma and sp_tails differ only in mode).
 // The single-pass tail search: the predictor, one correlation pass that sums rho^2 and keeps

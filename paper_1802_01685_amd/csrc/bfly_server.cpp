@@ -197,7 +197,7 @@ bool launch_tick(bf_server* s, Tick& t) {
     q.out.hist = (uint32_t*)(res + r->rl.hist);
     q.out.n_degenerate = (int64_t*)(res + r->rl.ndeg);
   }
-  fill_table(b, s->sp, sb.data(), nseg, s->slots, (BatchHdr*)t.table_pin);
+  fill_table(b, s->sp, sb.data(), nseg, s->slots, (BatchHdr*)t.table_pin, false);
   std::string err;
   hipError_t e = hipSuccess;
   for (int32_t i = 0; i < nseg && e == hipSuccess; ++i)

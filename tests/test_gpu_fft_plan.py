@@ -1,0 +1,39 @@
+"""FFT searches whose work ranges cut f0 bins (few blocks against few bins), against the same
+search with decimated spectrograms, whose ranges hold whole bins: maxima, argmax, histogram and
+spectrum equal bit for bit, the spectrogram's row blocks equal their maxima; and every offset
+against the FP64 oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import bfly_oracle as O  # noqa: E402
+from synth import BankParams, white_noise  # noqa: E402
+from tests.parity_util import check_against_oracle, to_np  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("grid", [(8, 64), (3, 200), (1, 257), (16, 16), (9, 97)])
+@pytest.mark.parametrize("lengths", [[3000], [9001, 700, 20000]])
+def test_ranges_that_cut_bins(grid, lengths):
+    from paper_1802_01685_amd import bfly as bf
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    p = BankParams(fs=600.0, L=600, n_f0=grid[0], n_fdot=grid[1], f0_min=20.0, f0_max=250.0,
+                   fdot_min=-100.0, fdot_max=120.0)
+    xs = [white_noise(n, n).astype(np.float32) for n in lengths]
+    xs[0][1500] = np.nan
+    xt = [torch.from_numpy(x).cuda() for x in xs]
+    bank = bf.bank_create(p, "fft")
+    cut = [to_np(o) for o in bf.search_batch(bank, xt, bf.make_params())]
+    whole = [to_np(o) for o in bf.search_batch(bank, xt, bf.make_params(t_block=4))]
+    for x, a, b in zip(xs, cut, whole):
+        for k in ("max_abs", "argmax", "hist", "spectrum", "n_degenerate"):
+            assert np.array_equal(a[k].view(np.uint8), b[k].view(np.uint8)), k
+        W = a["spec"].shape[1]
+        pad = np.zeros((grid[0], -(-W // 4) * 4), np.float32)
+        pad[:, :W] = a["spec"]
+        assert np.array_equal(pad.reshape(grid[0], -1, 4).max(2), b["spec"])
+        x64 = x.astype(np.float64)
+        check_against_oracle(x64, p, a, O.search(x64, p), "fft", f"cut/{grid}/{len(x)}")
