@@ -47,16 +47,31 @@ __global__ __launch_bounds__(256) void k_coinc_count(CoincSide b, CoincWork w, i
 }
 
 // In-place inclusive scan of start[1..W] by one 1024-thread work-group, so that start[t]
-// becomes the first slot of offset t's bucket; cursor[t] = start[t].
+// becomes the first slot of offset t's bucket; cursor[t] = start[t].  A round takes SCAN_E
+// entries per thread: read and written contiguously by the work-group, scanned from LDS (one
+// pad word per SCAN_E) where each thread sums consecutive ones: 34 us at 61,441 offsets and 64
+// at 126,001 (one entry per thread and round: 58 and 116).
+constexpr int SCAN_E = 8;
 __global__ __launch_bounds__(1024) void k_coinc_scan(CoincWork w, int64_t W) {
   __shared__ uint32_t part[16];
-  __shared__ uint32_t carry;
+  __shared__ uint32_t ent[1024 * (SCAN_E + 1)];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) carry = 0u;
-  __syncthreads();
-  for (int64_t base = 1; base <= W; base += 1024) {
-    const int64_t i = base + tid;
-    uint32_t v = i <= W ? w.start[i] : 0u;
+  uint32_t carry = 0u;
+  for (int64_t base = 1; base <= W; base += 1024 * SCAN_E) {
+#pragma unroll
+    for (int e = 0; e < SCAN_E; ++e) {
+      const int i = e * 1024 + tid;
+      ent[i + i / SCAN_E] = base + i <= W ? w.start[base + i] : 0u;
+    }
+    __syncthreads();
+    uint32_t* mine = ent + tid * (SCAN_E + 1);
+    uint32_t v = 0u;
+#pragma unroll
+    for (int e = 0; e < SCAN_E; ++e) {
+      v += mine[e];
+      mine[e] = v;     // inclusive within the thread
+    }
+    const uint32_t total = v;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const uint32_t u = __shfl_up(v, o, 64);
@@ -64,21 +79,25 @@ __global__ __launch_bounds__(1024) void k_coinc_scan(CoincWork w, int64_t W) {
     }
     if (lane == 63) part[wave] = v;
     __syncthreads();
-    if (tid == 0) {
-      uint32_t r = carry;
-      for (int k = 0; k < 16; ++k) {
-        const uint32_t t = part[k];
-        part[k] = r;
-        r += t;
-      }
-      carry = r;
+    uint32_t before = carry + v - total;   // everything before this thread's entries
+    for (int k = 0; k < 16; ++k) {
+      if (k < wave) before += part[k];
+      carry += part[k];
+    }
+#pragma unroll
+    for (int e = 0; e < SCAN_E; ++e) mine[e] += before;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < SCAN_E; ++e) {
+      const int i = e * 1024 + tid;
+      if (base + i > W) continue;
+      const uint32_t s = ent[i + i / SCAN_E];
+      w.start[base + i] = s;
+      if (base + i < W) w.cursor[base + i] = s;   // offset t's bucket begins at start[t]
     }
     __syncthreads();
-    v += part[wave];
-    if (i <= W) w.start[i] = v;
-    __syncthreads();
   }
-  for (int64_t t = tid; t < W; t += 1024) w.cursor[t] = w.start[t];
+  if (tid == 0) w.cursor[0] = 0u;
 }
 
 __global__ __launch_bounds__(256) void k_coinc_scatter(CoincSide b, CoincWork w, int64_t W) {
@@ -105,16 +124,17 @@ __global__ __launch_bounds__(256) void k_coinc_match(CoincSide a, CoincSide b, C
     const int64_t t_lo = ta - dtau > 0 ? ta - dtau : 0;
     const int64_t t_hi = ta + dtau < W - 1 ? ta + dtau : W - 1;
     unsigned long long pairs = 0ull;
-    for (int64_t t = t_lo; t <= t_hi; ++t) {
-      for (uint32_t s = w.start[t]; s < w.start[t + 1]; ++s) {
-        const uint32_t j = w.order[s];
-        const int64_t fib = (int64_t)b.k[j] / n_fdot;
-        if (b.k[j] < 0 || fib - g.f0_lo < 0 || fib - g.f0_lo >= n_bins) continue;
-        const double fb = grid_f0(g, fib);
-        if (fabs(fa - fb) <= df) {
-          ++pairs;
-          w.flag_b[j] = 1u;
-        }
+    // the buckets of consecutive offsets lie one after another: one range of slots (a loop over
+    // the offsets reads two bucket bounds for each, 68 us for 83 offsets around each tail)
+    const uint32_t s_hi = w.start[t_hi + 1];
+    for (uint32_t s = w.start[t_lo]; s < s_hi; ++s) {
+      const uint32_t j = w.order[s];
+      const int64_t fib = (int64_t)b.k[j] / n_fdot;
+      if (b.k[j] < 0 || fib - g.f0_lo < 0 || fib - g.f0_lo >= n_bins) continue;
+      const double fb = grid_f0(g, fib);
+      if (fabs(fa - fb) <= df) {
+        ++pairs;
+        w.flag_b[j] = 1u;
       }
     }
     if (pairs) {

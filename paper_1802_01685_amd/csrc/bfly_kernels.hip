@@ -409,7 +409,7 @@ __global__ __launch_bounds__(256) void k_prefix(const BatchHdr* __restrict__ hdr
       const double* o = tot + 5 * c;
       base = sums_add(base, {{o[0], o[1]}, {o[2], o[3]}, (int)o[4]});
     }
-    base = block_sums(base, part);
+    if (c_lo > 0) base = block_sums(base, part);
     for (int64_t c = c_lo; c < c_hi; ++c) {
       const int64_t i0 = c * PRE_CHUNK + (int64_t)tid * PRE_E;
       float v[PRE_E];
