@@ -1418,8 +1418,11 @@ __global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restr
 #pragma unroll
     for (int o = 0; o < NO; ++o) best[o] = 0.0;
     float2 h[8], h2;
+    // (k in a scalar register whatever the compiler made of the loops: a row address in vector
+    // registers turns every load into a loop over its distinct values, 14% at L = 2000)
     auto load_h = [&](int k) {
-      const __amdgpu_buffer_rsrc_t hr = row_rsrc(spectra + (int64_t)k * (M + 2));
+      const __amdgpu_buffer_rsrc_t hr =
+          row_rsrc(spectra + (int64_t)__builtin_amdgcn_readfirstlane(k) * (M + 2));
 #pragma unroll
       for (int s = 0; s < 8; ++s) h[s] = row_load2(hr, s < 4 ? va : vb, 4096u * s);
       h2 = row_load2(hr, 8u * (M / 2), 0u);
@@ -1535,7 +1538,7 @@ __global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restr
     };
     int bin = __builtin_amdgcn_readfirstlane(k_lo / nfd);
     for (int k0 = k_lo; k0 < k_hi; ++bin) {
-      const int k_end = min((bin + 1) * nfd, k_hi);
+      const int k_end = __builtin_amdgcn_readfirstlane(min((bin + 1) * nfd, k_hi));
       for (int k = k0; k < k_end; k += 2) {
         step(IntC<0>{}, k);
         if (k + 1 < k_end) step(IntC<1>{}, k + 1);
@@ -1579,7 +1582,8 @@ __global__ __launch_bounds__(512, 4) void k_fft4k_search(const BatchHdr* __restr
     if (dealt) {
       if (t == 0) taken = atomicAdd(const_cast<uint32_t*>(hdr->next) + (blockIdx.x & 7), 1u);
       __syncthreads();
-      item = (int64_t)gridDim.x + 8 * (int64_t)taken + (blockIdx.x & 7);
+      item = (int64_t)gridDim.x + 8 * (int64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)taken) +
+             (blockIdx.x & 7);
       __syncthreads();   // all have read it
     } else {
       item += gridDim.x;
