@@ -211,7 +211,7 @@ def roofline(res, p, prec, tile):
         achieved = flops / (ms * 1e-3) / 1e12
         return {"bound": "alu", "achieved": round(achieved, 2), "peak": PEAK_TFLOPS["fft"],
                 "unit": "TFLOP/s", "frac": round(achieved / PEAK_TFLOPS["fft"], 4),
-                "traffic": traffic, "counters": counters, "kernel": "k_fft_data+k_fft4k",
+                "traffic": traffic, "counters": counters, "kernel": "k_fft_data+k_fft4k_search",
                 "kernel_ms": round(ms, 3), "fft_points": 2 * m, "valid_per_block": valid,
                 "flop_per_launch": flops,
                 "effective_vs_fp32_peak": round(2.0 * p.L * res["corr_per_step"] /

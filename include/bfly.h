@@ -337,7 +337,8 @@ bf_status bf_server_destroy(bf_server* server);
 
 /* Work decomposition the searches would use for series of lengths n[0..n_segs-1] (host):
  * the bank sweep is split into *n_ranges contiguous ranges of whole f0 bins, and each
- * (series, block of offsets, range) is one work item of the contraction kernel. */
+ * (series, block of offsets, range) is one work item of the contraction kernel.  (A search of
+ * the FFT form with few blocks of offsets may cut the sweep into more ranges, inside bins.) */
 bf_status bf_plan(const bf_bank* bank, const int64_t* n, int32_t n_segs, int32_t* n_ranges,
                   int64_t* n_items);
 

@@ -597,7 +597,7 @@ int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots) {
 // step and shares their spectra through its L2, as many as fill the XCD's 64 work-groups q
 // times.  Taken where fft4k_cost falls by a twentieth and by k_bin_sums' 15 us, about 5
 // templates.  7 blocks against 48 bins of 200 templates: 336 items of 200 templates or 504 of
-// 133, 0.71 and 0.50 ms in the kernel.  Returns the ranges, 0 for whole bins.
+// 133, 0.71 and 0.50 ms in the kernel (1.09 and 0.88 ms for the search and its bank).  Returns the ranges, 0 for whole bins.
 int32_t plan_split_ranges(const BankDev& b, int64_t total_tiles, int slots, int32_t n_ranges) {
   const int64_t per_xcd = 2 * (int64_t)slots / 8;
   const double whole = fft4k_cost((total_tiles * n_ranges + 7) / 8, per_xcd,
@@ -647,7 +647,7 @@ int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, in
 // templates at a time) where it shortens the longest CU's work, in accumulator blocks, by a
 // tenth or more.  At 4 s of 512 Hz against a 16 x 16 bank the 2 x 4 tile makes 32 work items of
 // one 64-template tile each and the search takes 75 us in k_main, a quarter of the chip one
-// block after another; the 1 x 1 tile makes 104 items an eighth as long (14 us).  From a few
+// block after another; the 1 x 1 tile makes 104 items an eighth as long (20 us).  From a few
 // items per CU on the two tie and the 2 x 4 tile, which reads each fragment fewer times, stays.
 // The results do not depend on the shape in FP32.  (The other forms' strips carry scales or
 // schedules tied to their tile and stay as they are.)

@@ -304,7 +304,7 @@ __device__ __forceinline__ double block_sum_d(double v, double* red) {
 // templates and past its L taps) as z[n] = (h[2n], h[2n + 1]) in buf, taps past 2M added onto
 // the first ones.  Each thread forms its samples once (n = t + T i, at most 16 within the
 // transform) and keeps them for the mean, the norm and the staging: one float64 cosine per
-// sample is most of a bank's creation (65,536 x 4096: 3.1 ms with three, 1.6 ms with one).
+// sample is much of a bank's creation (65,536 x 4096: 3.06 ms with three, 2.07 ms with one).
 // Returns false for a template whose centred norm vanishes.
 template <int M>
 __device__ __forceinline__ bool stage_template(const GridDev& g, const BankDev& b, int64_t k,
@@ -1239,8 +1239,10 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
 // The plain search at M = 4096: the transform of k_fft4k, operation for operation (the same
 // values bit for bit), with 512 threads and 8 points per thread, so that two work-groups put
 // four waves on a SIMD.  Bound by VALU issue: 720,000 templates of L = 2000 against 2 x 126,001
-// offsets take 177 ms (227 ms with 256 threads of 16 points, two waves per SIMD: issue 77%
-// there, 97% here), 65,536 of L = 4096 against 126,977 offsets 13.0 ms (15.8 ms).
+// offsets took 177 ms in this layout against 227 ms with 256 threads of 16 points (two waves
+// per SIMD: VALU issue 77% there, 97% here), 65,536 of L = 4096 against 126,977 offsets 13.0
+// against 15.8 ms; with the shorter items of plan_fft_ranges, dealt as they are asked for, 170
+// and 11.3 ms.
 // * First pass: lanes 2i and 2i + 1 own the radix-8 butterflies i and 512 - i, each other's
 //   mirror under p -> M - p.  Each lane forms C = conj(H) X at its own 8 points and the four
 //   pairs whose lower-numbered slot (0..3) is its own; the partner's C and the partner's half
