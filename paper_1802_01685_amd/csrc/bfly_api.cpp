@@ -555,9 +555,18 @@ bf_status device_slots(int* slots) {
 // therefore pay until their set-up shows: 65,536 x 4096 on 31 blocks takes 12.6 ms with 16
 // ranges, 11.9 with 128 and 11.3 with 256; 720,000 x 2000 on 42 blocks 178 ms with 24 and
 // 170 ms with 240.
+//
+// Within a long item the work-groups of an XCD drift apart, the older ones ahead, and no longer
+// read the same spectra out of the caches: about 2% for each doubling past DRIFT templates (128
+// MB of spectra).  A large batch therefore goes on past 64 items per place while its ranges are
+// longer: 84 series against 512 bins of 512 templates take 5.9 s with 8 or 16 ranges, 5.7 with
+// 32, 5.5 with 64 and 5.6 with 128 or 256.
+constexpr int64_t DRIFT = 4096;
 double fft4k_cost(int64_t items_per_xcd, int64_t per_xcd, int64_t templates) {
   const double len = (double)templates, n = (double)items_per_xcd;
-  return items_per_xcd <= per_xcd ? 1.1 * len + 6.0 : n * (len + 6.0) / (double)per_xcd + 0.3 * len;
+  if (items_per_xcd <= per_xcd) return 1.1 * len + 6.0;
+  const double drift = templates > DRIFT ? 1.0 + 0.02 * std::log2(len / DRIFT) : 1.0;
+  return n * (len + 6.0) / (double)per_xcd * drift + 0.3 * len;
 }
 
 int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots) {
@@ -574,7 +583,7 @@ int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots) {
         best_cost = cost;
         best_r = r;
       }
-      if (items > 64 * conc) break;
+      if (items > 64 * conc && (int64_t)((b.n_bins + r - 1) / r) * b.n_fdot <= DRIFT) break;
     }
     return best_r;
   }
@@ -597,7 +606,8 @@ int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots) {
 // step and shares their spectra through its L2, as many as fill the XCD's 64 work-groups q
 // times.  Taken where fft4k_cost falls by a twentieth and by k_bin_sums' 15 us, about 5
 // templates.  7 blocks against 48 bins of 200 templates: 336 items of 200 templates or 504 of
-// 133, 0.71 and 0.50 ms in the kernel (1.09 and 0.88 ms for the search and its bank).  Returns the ranges, 0 for whole bins.
+// 133, 0.71 and 0.50 ms in the kernel (1.09 and 0.88 ms for the search and its bank).  Returns
+// the ranges, 0 for whole bins.
 int32_t plan_split_ranges(const BankDev& b, int64_t total_tiles, int slots, int32_t n_ranges) {
   const int64_t per_xcd = 2 * (int64_t)slots / 8;
   const double whole = fft4k_cost((total_tiles * n_ranges + 7) / 8, per_xcd,

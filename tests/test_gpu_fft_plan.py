@@ -37,3 +37,34 @@ def test_ranges_that_cut_bins(grid, lengths):
         assert np.array_equal(pad.reshape(grid[0], -1, 4).max(2), b["spec"])
         x64 = x.astype(np.float64)
         check_against_oracle(x64, p, a, O.search(x64, p), "fft", f"cut/{grid}/{len(x)}")
+
+
+@pytest.mark.parametrize("grid", [(32, 2100), (16, 4200)])
+def test_ranges_of_a_long_search(grid):
+    """More than 64 items per work-group: the ranges shrink towards 4096 templates.  The maxima,
+    argmax and spectra are those of the two half banks, whose plans differ, bit for bit."""
+    from paper_1802_01685_amd import bfly as bf
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    n = 4200 * (8193 - 64)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn(n, generator=gen, device="cuda")
+    got = []
+    for index, count in ((0, 1), (0, 2), (1, 2)):
+        p = BankParams(fs=64.0, L=64, n_f0=grid[0], n_fdot=grid[1], f0_min=2.0, f0_max=25.0,
+                       fdot_min=-10.0, fdot_max=10.0, shard_index=index, shard_count=count)
+        bank = bf.bank_create(p, "fft")
+        params = bf.make_params(t_block=4096)
+        if count == 1:
+            ranges, items = bf.plan(bank, [n])
+            assert ranges >= 16 and items == 4200 * ranges
+        out = bf.alloc_outputs(bank, n, params, x.device, want=("max_abs", "argmax", "spectrum"))
+        bf.search_segment(bank, x, params, out=out)
+        torch.cuda.synchronize()
+        got.append(out)
+        del bank
+    whole, lo, hi = got
+    upper = hi["max_abs"] > lo["max_abs"]
+    assert torch.equal(whole["max_abs"], torch.where(upper, hi["max_abs"], lo["max_abs"]))
+    assert torch.equal(whole["argmax"], torch.where(upper, hi["argmax"], lo["argmax"]))
+    assert torch.equal(whole["spectrum"], torch.cat([lo["spectrum"], hi["spectrum"]]))
