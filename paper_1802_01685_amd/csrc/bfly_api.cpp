@@ -569,6 +569,10 @@ double fft4k_cost(int64_t items_per_xcd, int64_t per_xcd, int64_t templates) {
   return n * (len + 6.0) / (double)per_xcd * drift + 0.3 * len;
 }
 
+// A launch has a work-group per item, of up to 512 threads (k_fft_data, k_fft4k_search), and HIP
+// takes fewer than 2^32 threads: 240 ranges of a 240 x 3000 bank on 35,000 blocks would be refused.
+constexpr int64_t MAX_FFT_ITEMS = (((int64_t)1 << 32) - 1) / 512;
+
 int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots) {
   double best_cost = 1e300;
   int32_t best_r = 1;
@@ -576,7 +580,7 @@ int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots) {
   if (b.fft_m == 4096 && b.n_bins >= 8) {
     for (int32_t r = 8; r <= b.n_bins; r += 8) {
       const int64_t items = total_tiles * r;
-      if (items > (int64_t)0x7FFFFFFF) break;
+      if (items > MAX_FFT_ITEMS) break;
       const double cost = fft4k_cost(total_tiles * (r / 8), conc / 8,
                                      (int64_t)((b.n_bins + r - 1) / r) * b.n_fdot);
       if (cost < best_cost * 0.999) {
@@ -589,7 +593,7 @@ int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots) {
   }
   for (int32_t r = 1; r <= b.n_bins; ++r) {
     const int64_t items = total_tiles * r;
-    if (items > (int64_t)0x7FFFFFFF) break;
+    if (items > MAX_FFT_ITEMS) break;
     const int64_t waves = (items + conc - 1) / conc;
     const double cost = (double)waves * (double)((b.n_bins + r - 1) / r) + 0.01 * (double)waves;
     if (cost < best_cost * 0.999) {

@@ -1,0 +1,23 @@
+// Prints the work decomposition of FFT searches, one line "<ranges> <items>" per line
+// "<bins> <templates per bin> <L> <blocks of offsets> <CUs>" on stdin.  Host code only: the
+// planner needs no device.
+#include "bfly_runtime.h"
+
+#include <cstdio>
+
+int main() {
+  int n_bins, n_fdot, L, slots;
+  long long blocks;
+  while (std::scanf("%d %d %d %lld %d", &n_bins, &n_fdot, &L, &blocks, &slots) == 5) {
+    bfly::BankDev b = {};
+    b.precision = bfly::P_FFT;
+    b.fft_m = 4096;
+    b.L = L;
+    b.n_bins = n_bins;
+    b.n_fdot = n_fdot;
+    b.K = (int64_t)n_bins * n_fdot;
+    const int32_t r = bfly::plan_fft_ranges(b, blocks, slots);
+    std::printf("%d %lld\n", r, blocks * r);
+  }
+  return 0;
+}

@@ -1,0 +1,45 @@
+"""The FFT form's work decomposition (host code, no GPU): tests/host/plan_print.cpp, linked to
+libbfly.so, prints the planner's ranges for banks and block counts too large to search here."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    from paper_1802_01685_amd import build as B
+    if not any(c and os.path.exists(c) for c in
+               (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", shutil.which("hipcc"))):
+        pytest.skip("no ROCm toolchain")
+    out = tmp_path_factory.mktemp("plan")
+    obj, exe = str(out / "plan_print.o"), str(out / "plan_print")
+    src = os.path.join(ROOT, "tests", "host", "plan_print.cpp")
+    for cmd in ([B._hipcc(), *B.COMMON, *B.DEVICE, "-c", src, "-o", obj],
+                [B._hipcc(), *B.DEVICE, obj, B.LIB, f"-Wl,-rpath,{os.path.dirname(B.LIB)}",
+                 "-o", exe]):
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-3000:]
+
+    def run(*shapes):
+        text = "".join(" ".join(str(v) for v in s) + "\n" for s in shapes)
+        r = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stderr[-3000:]
+        return [tuple(int(v) for v in line.split()) for line in r.stdout.splitlines()]
+
+    return run
+
+
+def test_items_fit_a_launch(plan):
+    """Batches of many blocks: a work-group of 512 threads per item stays below HIP's 2^32
+    threads, and the ranges remain a multiple of 8 (each XCD sweeps its own)."""
+    shapes = [(n_bins, n_fdot, L, blocks, 256)
+              for n_bins, n_fdot, L in ((240, 3000, 2000), (256, 1024, 64), (2880, 3000, 2000),
+                                        (9, 70000, 4096))
+              for blocks in (35000, 131072, 500000, 1000000)]
+    for s, (ranges, items) in zip(shapes, plan(*shapes)):
+        assert items * 512 < 2 ** 32, (s, ranges, items)
+        assert ranges % 8 == 0 and 8 <= ranges <= s[0], (s, ranges)
