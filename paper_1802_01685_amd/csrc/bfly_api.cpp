@@ -863,7 +863,7 @@ bf_status enqueue_onepass_tail_kernels(const bf_bank* bank, const SearchDev& sp_
   // the tails from the kept correlations (direct forms) or by transforming the listed (block,
   // template) pairs again (FFT form)
   if (b.precision == P_FFT)
-    HIP_TRY(launch_fft_pairs(table_dev, seg_slots, b, stream), "k_fft4k_pairs launch");
+    HIP_TRY(launch_fft_pairs(table_dev, b, stream), "k_fft4k_pairs launch");
   else
     HIP_TRY(launch_tails_keep(table_dev, seg_slots, b, stream), "k_tails_keep launch");
   // the tails pass over what the check flagged; every other work item returns at once

@@ -1612,8 +1612,11 @@ __global__ __launch_bounds__(256) void k_bin_sums(const BatchHdr* __restrict__ h
 // The tails of the (block, template) pairs the single pass of k_fft4k listed, for every
 // series not flagged (redo = 0; a flagged series gets the full tails pass instead).
 // Per pair the transform of k_fft4k with the same operations in the same order, so rho is
-// the same bit for bit, then the compare against kappa sigma_k.  Work unit = (series, shard
-// of the pair list); a work-group takes a shard's pairs one after another.  Two work-groups
+// the same bit for bit, then the compare against kappa sigma_k.  Work unit = a part of the pair
+// list of one (series, shard); a work-group takes its pairs one after another.  Only the shards
+// that hold templates count (64 templates each at least), a list has parts where there are fewer
+// lists than work-groups, and the work-groups take lists of different series, so that lists as
+// long as the bank (templates below their bound) do not fall to a few work-groups.  Two work-groups
 // per CU: within 256 registers only the block change (a few times per shard) reloads spilled
 // values.
 template <int SMAX>
@@ -1657,20 +1660,24 @@ __global__ __launch_bounds__(256, 2) void k_fft4k_pairs(const BatchHdr* __restri
 
   const unsigned va = 8u * (unsigned)t, vb = 8u * (512u - (unsigned)t);
   unsigned it = 0;   // pairs so far: the LDS buffers alternate as in k_fft4k
-  const int n_units = hdr->n_segs * CAND_SHARDS;
-  for (int unit = blockIdx.x; unit < n_units; unit += gridDim.x) {
-    const SegDesc& sg = segs[unit / CAND_SHARDS];
+  const int n_shards = (int)min(b.K_pad / 64, (int64_t)CAND_SHARDS);
+  const int n_lists = hdr->n_segs * n_shards;
+  const int parts = max((int)gridDim.x / n_lists, 1);
+  for (int unit = blockIdx.x; unit < n_lists * parts; unit += gridDim.x) {
+    const int shard = unit % n_lists / hdr->n_segs;
+    const SegDesc& sg = segs[(unit % hdr->n_segs + 37 * shard) % hdr->n_segs];
     if (!sg.redo || sg.redo[0] != 0u || !sg.c_tau) continue;
-    const int shard = unit % CAND_SHARDS;
     const int64_t per = sg.cand_cap / CAND_SHARDS;
-    const int64_t n = min((int64_t)sg.n_cand[shard], per);
-    if (n <= 0) continue;
+    const int64_t listed = min((int64_t)sg.n_cand[shard], per);
+    const int64_t j_lo = listed * (unit / n_lists) / parts;
+    const int64_t n = listed * (unit / n_lists + 1) / parts;
+    if (j_lo >= n) continue;
     // A shard's pairs come in runs of one block (a work-group appends the pairs of its
     // current block), so the block's spectrum and scales are reloaded only when the block
     // changes; the next pair's template spectrum is loaded while the current one transforms.
     const int64_t e0 = shard * per;
-    int64_t blk_n = sg.c_tau[e0];
-    int k_n = sg.c_k[e0];
+    int64_t blk_n = sg.c_tau[e0 + j_lo];
+    int k_n = sg.c_k[e0 + j_lo];
     float2 ha[8], hb[8], hha, hhb;
     auto load_h = [&](int k) {
       const __amdgpu_buffer_rsrc_t hr = row_rsrc(spectra + (int64_t)k * (M + 2));
@@ -1687,7 +1694,7 @@ __global__ __launch_bounds__(256, 2) void k_fft4k_pairs(const BatchHdr* __restri
     int tau_base = 0;
     float2 xa[8], xb[8];
     float sinv[NO];
-    for (int64_t j = 0; j < n; ++j, ++it) {
+    for (int64_t j = j_lo; j < n; ++j, ++it) {
       const int64_t blk = blk_n;
       const int k = k_n;
       if (blk != cur_blk) {
@@ -1873,9 +1880,8 @@ hipError_t launch_fft_pair_list(const BatchHdr* hdr, int32_t seg_slots, const Ba
   return hipGetLastError();
 }
 
-hipError_t launch_fft_pairs(const BatchHdr* hdr, int32_t seg_slots, const BankDev& b,
-                            hipStream_t s) {
-  const unsigned grid = (unsigned)std::min<int64_t>((int64_t)seg_slots * CAND_SHARDS, 512);
+hipError_t launch_fft_pairs(const BatchHdr* hdr, const BankDev& b, hipStream_t s) {
+  const unsigned grid = 512;   // two work-groups per CU, whatever the lists hold
   switch (fft4k_slots(b)) {
     case 9:
       hipLaunchKernelGGL(k_fft4k_pairs<9>, dim3(grid), dim3(256), 0, s, hdr, b);

@@ -298,8 +298,7 @@ bool fft_onepass_available(const BankDev& b);
 int contraction_wgs_per_cu(const BankDev& b, int tn);
 hipError_t launch_fft_pair_list(const BatchHdr* hdr, int32_t seg_slots, const BankDev& b,
                                 hipStream_t s);
-hipError_t launch_fft_pairs(const BatchHdr* hdr, int32_t seg_slots, const BankDev& b,
-                            hipStream_t s);
+hipError_t launch_fft_pairs(const BatchHdr* hdr, const BankDev& b, hipStream_t s);
 hipError_t launch_acf(const BatchHdr* hdr, int32_t seg_slots, int L, hipStream_t s);
 hipError_t launch_qspec(const BatchHdr* hdr, int32_t seg_slots, int L, int pred_n,
                         hipStream_t s);

@@ -158,6 +158,15 @@ __global__ __launch_bounds__(1024) void k_qspec(const BatchHdr* __restrict__ hdr
   }
 }
 
+// FFT form: a series that lists more than PAIRS_MOST of its (block, template) pairs gets the whole
+// tails pass instead, if that pass has work for every CU.  A listed pair takes 1.2 to 1.4 times as
+// long as one of the whole pass, which sweeps a block's templates in order: with every pair listed
+// 15.9 against 9.3 ms at 1000 series x 1024 templates, 22.1 against 17.6 at 150 x 5,874 (66 x 89).
+// With few work items the list is the faster one, 0.83 against 2.24 ms at 64 bins of 512 templates
+// on 2 blocks (128 items).
+constexpr double PAIRS_MOST = 0.75;
+constexpr int64_t PAIRS_MIN_ITEMS = 512;
+
 // Per series: REDO_ALL if the candidates of a shard did not fit; direct forms: REDO_TILES if an
 // exact threshold lies below its predicted lower one, with the first bound of each such tile
 // of TILE_K templates overwritten by -1 (bounds are not negative).  One wave per tile.
@@ -168,7 +177,19 @@ __global__ __launch_bounds__(256) void k_tails_check(const BatchHdr* __restrict_
   const int64_t per = sg.cand_cap / CAND_SHARDS;
   if (blockIdx.x == 0 && threadIdx.x < CAND_SHARDS && (int64_t)sg.n_cand[threadIdx.x] > per)
     atomicOr(sg.redo, REDO_ALL);
-  if (b.precision == P_FFT) return;   // k_fft_pair_list lists those templates' blocks
+  if (b.precision == P_FFT) {   // k_fft_pair_list has listed those templates' blocks
+    if (blockIdx.x == 0 && hdr->n_items >= PAIRS_MIN_ITEMS) {
+      static_assert(CAND_SHARDS == 256, "one thread per shard");
+      __shared__ unsigned int listed;
+      if (threadIdx.x == 0) listed = 0u;
+      __syncthreads();
+      atomicAdd(&listed, (unsigned int)sg.n_cand[threadIdx.x]);
+      __syncthreads();
+      if (threadIdx.x == 0 && (double)listed > PAIRS_MOST * (double)b.K * (double)sg.n_tiles)
+        atomicOr(sg.redo, REDO_ALL);
+    }
+    return;
+  }
   static_assert(TILE_K == WAVE, "one lane per template of a tile");
   const int lane = threadIdx.x & 63;
   const int64_t n_tiles = b.K_pad / TILE_K;
