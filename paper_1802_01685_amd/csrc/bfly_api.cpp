@@ -833,7 +833,7 @@ bf_status enqueue_tail_kernels(const BankDev& b, const SearchDev& sp_sigma,
 }
 
 bf_status enqueue_onepass_tail_kernels(const bf_bank* bank, const SearchDev& sp_pass,
-                                       const SearchDev& sp_tails, const BatchHdr* table_dev,
+                                       const SearchDev& sp_tails, BatchHdr* table_dev,
                                        int32_t seg_slots, int32_t x_blocks, int64_t max_n, int64_t main_blocks,
                                        float margin, hipStream_t stream, TimingSet* te) {
   const BankDev& b = bank->dev;

@@ -164,7 +164,7 @@ struct BatchHdr {
   int64_t total_tiles;  // sum of n_tiles over the series
   int64_t n_items;      // total_tiles * n_ranges
   int32_t split;        // 1: ranges of templates that may cut bins (k_fft4k_search only)
-  int32_t reserved0;
+  uint32_t redo_any;    // single-pass tail search: 1 once a series has REDO_ALL (0 as uploaded)
   uint32_t next[8];     // k_fft4k_search with fewer work-groups than items: items taken per XCD
                         // beyond the first of each work-group (0 in an uploaded table)
 };
@@ -304,7 +304,7 @@ hipError_t launch_qspec(const BatchHdr* hdr, int32_t seg_slots, int L, int pred_
                         hipStream_t s);
 hipError_t launch_pred(const BatchHdr* hdr, int32_t seg_slots, const GridDev& g,
                        const BankDev& b, float kappa, float margin, hipStream_t s);
-hipError_t launch_tails_check(const BatchHdr* hdr, int32_t seg_slots, const BankDev& b,
+hipError_t launch_tails_check(BatchHdr* hdr, int32_t seg_slots, const BankDev& b,
                               hipStream_t s);
 hipError_t launch_tails_keep(const BatchHdr* hdr, int32_t seg_slots, const BankDev& b,
                              hipStream_t s);

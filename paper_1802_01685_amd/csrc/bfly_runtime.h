@@ -142,7 +142,7 @@ bf_status enqueue_kernels(const BankDev& b, const SearchDev& sp, const BatchHdr*
 // thresholds, the check and the selection of the tails, and the tails pass for the series
 // whose check failed (its work-groups return at once for the others).
 bf_status enqueue_onepass_tail_kernels(const bf_bank* bank, const SearchDev& sp_pass,
-                                       const SearchDev& sp_tails, const BatchHdr* table_dev,
+                                       const SearchDev& sp_tails, BatchHdr* table_dev,
                                        int32_t seg_slots, int32_t x_blocks, int64_t max_n,
                           int64_t main_blocks,
                                        float margin, hipStream_t stream, TimingSet* te);

@@ -158,6 +158,11 @@ __global__ __launch_bounds__(1024) void k_qspec(const BatchHdr* __restrict__ hdr
   }
 }
 
+__device__ __forceinline__ void flag_all(BatchHdr* hdr, const SegDesc& sg) {
+  atomicOr(sg.redo, REDO_ALL);
+  hdr->redo_any = 1u;
+}
+
 // FFT form: a series that lists more than PAIRS_MOST of its (block, template) pairs gets the whole
 // tails pass instead, if that pass has work for every CU.  A listed pair takes 1.2 to 1.4 times as
 // long as one of the whole pass, which sweeps a block's templates in order: with every pair listed
@@ -170,13 +175,13 @@ constexpr int64_t PAIRS_MIN_ITEMS = 512;
 // Per series: REDO_ALL if the candidates of a shard did not fit; direct forms: REDO_TILES if an
 // exact threshold lies below its predicted lower one, with the first bound of each such tile
 // of TILE_K templates overwritten by -1 (bounds are not negative).  One wave per tile.
-__global__ __launch_bounds__(256) void k_tails_check(const BatchHdr* __restrict__ hdr, BankDev b) {
+__global__ __launch_bounds__(256) void k_tails_check(BatchHdr* __restrict__ hdr, BankDev b) {
   if ((int)blockIdx.y >= hdr->n_segs) return;
   const SegDesc& sg = hdr_segs(hdr)[blockIdx.y];
   if (!sg.redo) return;
   const int64_t per = sg.cand_cap / CAND_SHARDS;
   if (blockIdx.x == 0 && threadIdx.x < CAND_SHARDS && (int64_t)sg.n_cand[threadIdx.x] > per)
-    atomicOr(sg.redo, REDO_ALL);
+    flag_all(hdr, sg);
   if (b.precision == P_FFT) {   // k_fft_pair_list has listed those templates' blocks
     if (blockIdx.x == 0 && hdr->n_items >= PAIRS_MIN_ITEMS) {
       static_assert(CAND_SHARDS == 256, "one thread per shard");
@@ -186,7 +191,7 @@ __global__ __launch_bounds__(256) void k_tails_check(const BatchHdr* __restrict_
       atomicAdd(&listed, (unsigned int)sg.n_cand[threadIdx.x]);
       __syncthreads();
       if (threadIdx.x == 0 && (double)listed > PAIRS_MOST * (double)b.K * (double)sg.n_tiles)
-        atomicOr(sg.redo, REDO_ALL);
+        flag_all(hdr, sg);
     }
     return;
   }
@@ -259,7 +264,7 @@ hipError_t launch_qspec(const BatchHdr* hdr, int32_t seg_slots, int L, int pred_
   return hipGetLastError();
 }
 
-hipError_t launch_tails_check(const BatchHdr* hdr, int32_t seg_slots, const BankDev& b,
+hipError_t launch_tails_check(BatchHdr* hdr, int32_t seg_slots, const BankDev& b,
                               hipStream_t s) {
   const int64_t xb = (b.K_pad + 255) / 256;
   hipLaunchKernelGGL(k_tails_check, dim3((unsigned)(xb < 1024 ? (xb > 0 ? xb : 1) : 1024), (unsigned)seg_slots),
