@@ -124,8 +124,11 @@ __global__ __launch_bounds__(256) void k_acf_sum(const BatchHdr* __restrict__ hd
 }
 
 // Q(f) = R(0) + 2 sum_{l=1}^{L-1} R(l) cos(2 pi f l / N), f = 0 .. N/2, N a power of two.  A
-// block takes 64 frequencies, one per lane, and each of its 16 waves a sixteenth of the lags
-// (one thread per frequency over all lags took 175 us at L = 4096; this 27 us).
+// block takes 64 frequencies at a time, one per lane, and each of its 16 waves a sixteenth of the
+// lags (one thread per frequency over all lags took 175 us at L = 4096; this 27 us).  With many
+// series a block takes more frequencies, up to all of a series (launch_qspec): with a table for
+// every 64 frequencies 1,000 series of L = 600 took 2.0 ms and 4,000 of L = 64 5.0, this 0.96 and
+// 0.80.
 constexpr int QSPEC_WAVES = 16;
 __global__ __launch_bounds__(1024) void k_qspec(const BatchHdr* __restrict__ hdr, int L, int N) {
   if ((int)blockIdx.y >= hdr->n_segs) return;
@@ -142,19 +145,22 @@ __global__ __launch_bounds__(1024) void k_qspec(const BatchHdr* __restrict__ hdr
   for (int l = threadIdx.x; l < L; l += 1024) rl[l] = l ? 2.0 * sg.acf[l] : sg.acf[0];
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int f = (int)blockIdx.x * 64 + lane;
   const int lmax = L < N ? L : N;
   const int per = (lmax + QSPEC_WAVES - 1) / QSPEC_WAVES;
   const int hi = (wave + 1) * per < lmax ? (wave + 1) * per : lmax;
-  double q = 0.0;
-  for (int l = wave * per; l < hi; ++l)
-    q = fma(rl[l], (double)ct[(f * l) & (N - 1)], q);
-  part[wave][lane] = q;
-  __syncthreads();
-  if (wave == 0 && f <= N / 2) {
-    double s = 0.0;
-    for (int w = 0; w < QSPEC_WAVES; ++w) s += part[w][lane];
-    sg.qspec[f] = (float)s;
+  for (int f0 = (int)blockIdx.x * 64; f0 <= N / 2; f0 += (int)gridDim.x * 64) {
+    const int f = f0 + lane;
+    double q = 0.0;
+    for (int l = wave * per; l < hi; ++l)
+      q = fma(rl[l], (double)ct[(f * l) & (N - 1)], q);
+    part[wave][lane] = q;
+    __syncthreads();
+    if (wave == 0 && f <= N / 2) {
+      double s = 0.0;
+      for (int w = 0; w < QSPEC_WAVES; ++w) s += part[w][lane];
+      sg.qspec[f] = (float)s;
+    }
+    __syncthreads();   // the next frequencies overwrite the sums
   }
 }
 
@@ -259,8 +265,21 @@ hipError_t launch_acf(const BatchHdr* hdr, int32_t seg_slots, int L, hipStream_t
 
 hipError_t launch_qspec(const BatchHdr* hdr, int32_t seg_slots, int L, int pred_n,
                         hipStream_t s) {
-  hipLaunchKernelGGL(k_qspec, dim3((unsigned)((pred_n / 2 + 1 + 63) / 64), (unsigned)seg_slots),
-                     dim3(64 * QSPEC_WAVES), 0, s, hdr, L, pred_n);
+  const int groups = (pred_n / 2 + 1 + 63) / 64;
+  // groups of 64 frequencies per block: the fewest rounds of 256 blocks (one per CU) times a
+  // block's time, 5 us for its table and 0.35 + 0.0054 L us per group, in units of the last
+  int xb = groups;
+  int64_t best = INT64_MAX;
+  for (int x = groups; x >= 1; --x) {
+    const int64_t rounds = ((int64_t)x * seg_slots + 255) / 256;
+    const int64_t cost = rounds * ((groups + x - 1) / x * (int64_t)(L + 65) + 925);
+    if (cost < best) {
+      best = cost;
+      xb = x;
+    }
+  }
+  hipLaunchKernelGGL(k_qspec, dim3((unsigned)xb, (unsigned)seg_slots), dim3(64 * QSPEC_WAVES), 0, s,
+                     hdr, L, pred_n);
   return hipGetLastError();
 }
 

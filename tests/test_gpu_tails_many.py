@@ -48,3 +48,34 @@ def test_idle_tails_pass(stages):
     once: less than the contraction, which transforms all 256,000 pairs.  With every work-group of
     the tails pass looking through all the series it took many times as long."""
     assert stages["finalize"] < stages["main"]
+
+
+@pytest.mark.parametrize("L,series", [(64, 700), (600, 90), (4096, 9)])
+def test_predictor_of_many_series(L, series):
+    """A series' part of the workspace, the predictor's lag sums, cosine transform and bounds and
+    the pair lists among it, comes out the same bit for bit alone and in a batch, where one
+    work-group forms several or all of the series' frequencies."""
+    from paper_1802_01685_amd import bfly as bf
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    p = BankParams(fs=float(L), L=L, n_f0=4, n_fdot=9, f0_min=0.05 * L, f0_max=0.4 * L,
+                   fdot_min=-0.2 * L, fdot_max=0.2 * L)
+    bank = bf.bank_create(p, "fft")
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    n = 3 * L
+    x = torch.randn(n, generator=gen, device="cuda")
+    prm = bf.make_params()
+    # 256 more series add 256 table entries (of 256 to 511 bytes each) and parts (whole 256 bytes)
+    size = [bf.tails_workspace_bytes(bank, [n] * k, prm) for k in (1, 257)]
+    part = (size[1] - size[0]) // 256 // 256 * 256 - 256
+
+    def parts(k):
+        ws = torch.zeros(bf.tails_workspace_bytes(bank, [n] * k, prm), dtype=torch.uint8,
+                         device="cuda")
+        bf.search_tails(bank, [x] * k, 3.0, 1 << 12, prm, workspace=ws)
+        torch.cuda.synchronize()
+        return ws[ws.numel() - k * part:].reshape(k, part)
+
+    one = parts(1)
+    assert one.any()
+    assert torch.equal(parts(series), one.expand(series, part))
