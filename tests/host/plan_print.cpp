@@ -1,14 +1,15 @@
 // Prints the work decomposition of FFT searches, one line "<ranges> <items>" per line
-// "<bins> <templates per bin> <L> <blocks of offsets> <CUs>" on stdin.  Host code only: the
+// "<bins> <templates per bin> <L> <blocks of offsets> <CUs> <tails>" on stdin (tails: 1 for a tail
+// search).  Host code only: the
 // planner needs no device.
 #include "bfly_runtime.h"
 
 #include <cstdio>
 
 int main() {
-  int n_bins, n_fdot, L, slots;
+  int n_bins, n_fdot, L, slots, tails;
   long long blocks;
-  while (std::scanf("%d %d %d %lld %d", &n_bins, &n_fdot, &L, &blocks, &slots) == 5) {
+  while (std::scanf("%d %d %d %lld %d %d", &n_bins, &n_fdot, &L, &blocks, &slots, &tails) == 6) {
     bfly::BankDev b = {};
     b.precision = bfly::P_FFT;
     b.fft_m = 4096;
@@ -16,7 +17,8 @@ int main() {
     b.n_bins = n_bins;
     b.n_fdot = n_fdot;
     b.K = (int64_t)n_bins * n_fdot;
-    const int32_t r = bfly::plan_fft_ranges(b, blocks, slots);
+    const int32_t r = bfly::plan_fft_ranges(b, blocks, slots,
+                                            tails ? bfly::MODE_ONEPASS : bfly::MODE_SEARCH);
     std::printf("%d %lld\n", r, blocks * r);
   }
   return 0;
