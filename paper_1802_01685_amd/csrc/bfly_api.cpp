@@ -574,29 +574,33 @@ double fft4k_cost(int64_t items_per_xcd, int64_t per_xcd, int64_t templates) {
 constexpr int64_t MAX_FFT_ITEMS = (((int64_t)1 << 32) - 1) / 512;
 
 // k_fft4k (a tail search's passes) has two waves on a SIMD instead of four and shares a CU more
-// evenly: its time goes by whole rounds of the largest item, with about 4 templates of set-up.
-// Of plans within 3%, the one of the shortest items.  By fft4k_cost 200 blocks against 16 bins of
-// 64 templates took 2.67 ms on 8 ranges, this rule's 16 take 2.37; 80 blocks against 99 bins of 16
-// 2.27 and 2.23, 100 against 300 of 5 4.34 and 3.95; over 22 such shapes its choice is on average
-// 0.5% behind the best of the multiples of 8 up to 512, by fft4k_cost 2.2% and by rounds of bins
-// alone 2.4%.  The tails of a 64 s light curve against 60 bins of 3,000 templates take 40.9 ms
-// instead of 50.8.
-double fft4k_rounds(int64_t items_per_xcd, int64_t per_xcd, int64_t templates) {
-  return (double)((items_per_xcd + per_xcd - 1) / per_xcd) * ((double)templates + 4.0);
+// evenly: its time goes by whole rounds of the largest item, with about 4 templates of set-up, and
+// 8 for each bin's end into decimated spectrogram rows (atomics).  Of plans within 3%, the one of
+// the shortest items.  By fft4k_cost 200 blocks against 16 bins of 64 templates took 2.67 ms on 8
+// ranges, this rule's 16 take 2.37; 100 against 300 of 5 4.34 and 4.03; 40 against 201 templates
+// with t_block = 16 0.60 and 0.55.  Over 43 such shapes its choice is on average 2.5% behind the
+// best of the multiples of 8 up to 512, by fft4k_cost 7.2% and by rounds of bins alone 3.6%.  The
+// tails of a 64 s light curve against 60 bins of 3,000 templates take 40.9 ms instead of 50.8.
+double fft4k_rounds(int64_t items_per_xcd, int64_t per_xcd, int64_t bins, int64_t n_fdot,
+                    bool decimated) {
+  return (double)((items_per_xcd + per_xcd - 1) / per_xcd) *
+         ((double)(bins * (n_fdot + (decimated ? 8 : 0))) + 4.0);
 }
 
-int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots, int mode) {
+int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots, const SearchDev& sp) {
   double best_cost = 1e300;
   int32_t best_r = 1;
   const int64_t conc = 2 * (int64_t)slots;
+  const bool search = sp.mode == MODE_SEARCH;
   if (b.fft_m == 4096 && b.n_bins >= 8) {
     for (int32_t r = 8; r <= b.n_bins; r += 8) {
       const int64_t items = total_tiles * r;
       if (items > MAX_FFT_ITEMS) break;
-      const int64_t templates = (int64_t)((b.n_bins + r - 1) / r) * b.n_fdot;
-      const double cost = (mode == MODE_SEARCH ? fft4k_cost : fft4k_rounds)(total_tiles * (r / 8),
-                                                                           conc / 8, templates);
-      if (cost < best_cost * (mode == MODE_SEARCH ? 0.999 : 1.03)) {
+      const int64_t bins = (b.n_bins + r - 1) / r, templates = bins * b.n_fdot;
+      const double cost =
+          search ? fft4k_cost(total_tiles * (r / 8), conc / 8, templates)
+                 : fft4k_rounds(total_tiles * (r / 8), conc / 8, bins, b.n_fdot, sp.t_block > 1);
+      if (cost < best_cost * (search ? 0.999 : 1.03)) {
         best_cost = std::min(best_cost, cost);
         best_r = r;
       }
@@ -758,7 +762,7 @@ TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s,
   std::memset(hdr, 0, sizeof(BatchHdr));
   hdr->n_segs = n;
   hdr->total_tiles = tiles;
-  hdr->n_ranges = b.precision == P_FFT ? plan_fft_ranges(b, tiles, slots, sp.mode)
+  hdr->n_ranges = b.precision == P_FFT ? plan_fft_ranges(b, tiles, slots, sp)
                                        : plan_ranges(b, tiles, slots, sp.tm, sp.tn);
   if (b.precision == P_FFT && may_split && all_spec && fft_can_split_bins(b, sp)) {
     const int32_t r = plan_split_ranges(b, tiles, slots, hdr->n_ranges);
@@ -1180,7 +1184,7 @@ bf_status bf_plan(const bf_bank* bank, const int64_t* n, int32_t n_segs, int32_t
     for (int32_t i = 0; i < n_segs; ++i)
       tiles += (n[i] - bank->dev.L + 1 + sp.n_wg - 1) / sp.n_wg;
     const int32_t r = bank->dev.precision == P_FFT
-                          ? plan_fft_ranges(bank->dev, tiles, slots, MODE_SEARCH)
+                          ? plan_fft_ranges(bank->dev, tiles, slots, sp)
                           : plan_ranges(bank->dev, tiles, slots, sp.tm, sp.tn);
     if (n_ranges) *n_ranges = r;
     if (n_items) *n_items = tiles * r;

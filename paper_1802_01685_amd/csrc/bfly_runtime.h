@@ -81,8 +81,8 @@ int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, in
 // Changes the default tile where the series are too small for it (never one chosen by BF_TILE).
 void fit_tile(const BankDev& b, const bf_segment* segs, int32_t n_segs, int slots,
               SearchDev* sp);
-// mode: MODE_SEARCH, or a pass of a tail search, whose kernel has another cost.
-int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots, int mode);
+// The plan depends on the search's mode (a tail search's kernel has another cost) and t_block.
+int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots, const SearchDev& sp);
 // FFT form: overlap-save blocks of a series with W offsets.
 inline int64_t fft_blocks(const BankDev& b, int64_t W) {
   const int64_t v = 2 * (int64_t)b.fft_m - b.L + 1;

@@ -1,15 +1,15 @@
 // Prints the work decomposition of FFT searches, one line "<ranges> <items>" per line
-// "<bins> <templates per bin> <L> <blocks of offsets> <CUs> <tails>" on stdin (tails: 1 for a tail
-// search).  Host code only: the
-// planner needs no device.
+// "<bins> <templates per bin> <L> <blocks of offsets> <CUs> <tails> <t_block>" on stdin (tails: 1
+// for a tail search).  Host code only: the planner needs no device.
 #include "bfly_runtime.h"
 
 #include <cstdio>
 
 int main() {
-  int n_bins, n_fdot, L, slots, tails;
+  int n_bins, n_fdot, L, slots, tails, t_block;
   long long blocks;
-  while (std::scanf("%d %d %d %lld %d %d", &n_bins, &n_fdot, &L, &blocks, &slots, &tails) == 6) {
+  while (std::scanf("%d %d %d %lld %d %d %d", &n_bins, &n_fdot, &L, &blocks, &slots, &tails,
+                    &t_block) == 7) {
     bfly::BankDev b = {};
     b.precision = bfly::P_FFT;
     b.fft_m = 4096;
@@ -17,8 +17,10 @@ int main() {
     b.n_bins = n_bins;
     b.n_fdot = n_fdot;
     b.K = (int64_t)n_bins * n_fdot;
-    const int32_t r = bfly::plan_fft_ranges(b, blocks, slots,
-                                            tails ? bfly::MODE_ONEPASS : bfly::MODE_SEARCH);
+    bfly::SearchDev sp = {};
+    sp.mode = tails ? bfly::MODE_ONEPASS : bfly::MODE_SEARCH;
+    sp.t_block = t_block;
+    const int32_t r = bfly::plan_fft_ranges(b, blocks, slots, sp);
     std::printf("%d %lld\n", r, blocks * r);
   }
   return 0;

@@ -36,7 +36,7 @@ def plan(tmp_path_factory):
 def test_items_fit_a_launch(plan):
     """Batches of many blocks: a work-group of 512 threads per item stays below HIP's 2^32
     threads, and the ranges remain a multiple of 8 (each XCD sweeps its own)."""
-    shapes = [(n_bins, n_fdot, L, blocks, 256, tails)
+    shapes = [(n_bins, n_fdot, L, blocks, 256, tails, 1)
               for n_bins, n_fdot, L in ((240, 3000, 2000), (256, 1024, 64), (2880, 3000, 2000),
                                         (9, 70000, 4096))
               for blocks in (35000, 131072, 500000, 1000000) for tails in (0, 1)]
@@ -45,18 +45,32 @@ def test_items_fit_a_launch(plan):
         assert ranges % 8 == 0 and 8 <= ranges <= s[0], (s, ranges)
 
 
-# bins, templates per bin, L, blocks: the ranges within 5% of the fastest of 8, 16, 24, 32, 40, 48,
-# 64, 96, 128, ... 512, in the single pass of a tail search on an MI355X
-TAIL_PLANS = {(16, 64, 600, 200): {16}, (16, 64, 600, 1000): {8, 16},
-              (502, 1, 1024, 300): {8, 16, 24, 32, 40, 48}, (300, 5, 1024, 100): {24, 40},
-              (64, 30, 2000, 40): {64}, (66, 89, 512, 300): {8, 24, 40}, (48, 200, 1024, 5): {48},
-              (249, 9, 37, 40): {24, 64}, (256, 256, 4096, 30): {256},
-              (64, 64, 4096, 120): {8, 16, 24, 32, 40, 48, 64}, (240, 300, 2000, 42): {24, 48, 240},
-              (64, 512, 2000, 2): {64}, (24, 100, 2000, 48): {8, 24}, (16, 16, 600, 1000): {8},
-              (240, 3000, 2000, 11): {40, 240}, (512, 16, 2000, 15): {32, 64, 96, 128, 192, 256}}
+# bins, templates per bin, L, blocks, t_block: the ranges within 5% of the fastest of 8, 16, 24, 32,
+# 40, 48, 64, 96, 128, ... 512, in the single pass of a tail search on an MI355X
+TAIL_PLANS = {
+    (16, 64, 600, 200, 1): {16},
+    (16, 64, 600, 1000, 1): {8, 16},
+    (502, 1, 1024, 300, 1): {8, 16, 24, 32, 40, 48},
+    (300, 5, 1024, 100, 1): {24, 40},
+    (64, 30, 2000, 40, 1): {64},
+    (66, 89, 512, 300, 1): {8, 24, 40},
+    (48, 200, 1024, 5, 1): {48},
+    (249, 9, 37, 40, 1): {24, 64},
+    (256, 256, 4096, 30, 1): {256},
+    (64, 64, 4096, 120, 1): {8, 16, 24, 32, 40, 48, 64},
+    (240, 300, 2000, 42, 1): {24, 48, 240},
+    (64, 512, 2000, 2, 1): {64},
+    (24, 100, 2000, 48, 1): {8, 24},
+    (16, 16, 600, 1000, 1): {8},
+    (240, 3000, 2000, 11, 1): {40, 240},
+    (512, 16, 2000, 15, 1): {32, 64, 96, 128, 192, 256},
+    (64, 30, 2000, 40, 16): {24, 32, 64},
+    (99, 16, 600, 80, 16): {32, 40, 56, 64},
+    (96, 3, 512, 40, 16): {24, 48},
+}
 
 
 def test_tail_plans(plan):
-    shapes = [s + (256, 1) for s in TAIL_PLANS]
-    got = {s[:4]: r for s, (r, _) in zip(shapes, plan(*shapes))}
-    assert all(got[s] in TAIL_PLANS[s] for s in TAIL_PLANS), got
+    shapes = [s[:4] + (256, 1, s[4]) for s in TAIL_PLANS]
+    got = {s: r for s, (r, _) in zip(TAIL_PLANS, plan(*shapes))}
+    assert {s: r for s, r in got.items() if r not in TAIL_PLANS[s]} == {}
