@@ -335,10 +335,13 @@ bf_status bf_server_stats(bf_server* server, int64_t* done, int64_t* ticks,
  * lost. */
 bf_status bf_server_destroy(bf_server* server);
 
-/* Work decomposition the searches would use for series of lengths n[0..n_segs-1] (host):
- * the bank sweep is split into *n_ranges contiguous ranges of whole f0 bins, and each
- * (series, block of offsets, range) is one work item of the contraction kernel.  (A search of
- * the FFT form with few blocks of offsets may cut the sweep into more ranges, inside bins.) */
+/* Work decomposition that bf_search_batch would use for series of lengths n[0..n_segs-1] with
+ * t_block = 1 and a spectrogram for each (host): the bank sweep is split into *n_ranges
+ * contiguous ranges, and each (series, block of offsets, range) is one work item of the
+ * contraction kernel.  Ranges hold whole f0 bins, except in searches of the FFT form with few
+ * blocks of offsets, whose ranges may cut bins; there a search with t_block > 1 or without a
+ * spectrogram keeps whole bins, in other numbers.  Tail searches and the server decompose their
+ * work by plans of their own. */
 bf_status bf_plan(const bf_bank* bank, const int64_t* n, int32_t n_segs, int32_t* n_ranges,
                   int64_t* n_items);
 

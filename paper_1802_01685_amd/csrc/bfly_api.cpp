@@ -702,6 +702,18 @@ void fit_tile(const BankDev& b, const bf_segment* segs, int32_t n_segs, int slot
   }
 }
 
+// The ranges of a search.  *split: they may cut bins (where may_split allows it).
+static int32_t plan(const BankDev& b, const SearchDev& sp, int64_t total_tiles, int slots,
+                    bool may_split, bool* split) {
+  *split = false;
+  if (b.precision != P_FFT) return plan_ranges(b, total_tiles, slots, sp.tm, sp.tn);
+  const int32_t whole = plan_fft_ranges(b, total_tiles, slots, sp);
+  if (!may_split || !fft_can_split_bins(b, sp)) return whole;
+  const int32_t cut = plan_split_ranges(b, total_tiles, slots, whole);
+  *split = cut > 0;
+  return cut > 0 ? cut : whole;
+}
+
 TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s, int32_t n,
                      int slots, BatchHdr* hdr, bool may_split) {
   TableInfo ti;
@@ -762,16 +774,8 @@ TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s,
   std::memset(hdr, 0, sizeof(BatchHdr));
   hdr->n_segs = n;
   hdr->total_tiles = tiles;
-  hdr->n_ranges = b.precision == P_FFT ? plan_fft_ranges(b, tiles, slots, sp)
-                                       : plan_ranges(b, tiles, slots, sp.tm, sp.tn);
-  if (b.precision == P_FFT && may_split && all_spec && fft_can_split_bins(b, sp)) {
-    const int32_t r = plan_split_ranges(b, tiles, slots, hdr->n_ranges);
-    if (r > 0) {
-      hdr->n_ranges = r;
-      hdr->split = 1;
-      ti.split = true;
-    }
-  }
+  hdr->n_ranges = plan(b, sp, tiles, slots, may_split && all_spec, &ti.split);
+  hdr->split = ti.split;
   hdr->n_items = tiles * hdr->n_ranges;
   ti.n_items = hdr->n_items;
   return ti;
@@ -1168,24 +1172,22 @@ bf_status bf_kernel_times(double* ms, int32_t* n_searches) {
 bf_status bf_plan(const bf_bank* bank, const int64_t* n, int32_t n_segs, int32_t* n_ranges,
                   int64_t* n_items) {
   if (!bank || !n || n_segs < 1) return fail(BF_EINVAL, "bad arguments");
-  int64_t tiles = 0;
+  for (int32_t i = 0; i < n_segs; ++i)
+    if (n[i] < bank->dev.L) return fail(BF_EINVAL, "series shorter than L");
   int slots = 0;
   bf_status st = device_slots(&slots);
   if (st != BF_OK) return st;
   try {
     std::vector<bf_segment> segs((size_t)n_segs);
-    for (int32_t i = 0; i < n_segs; ++i) {
-      if (n[i] < bank->dev.L) return fail(BF_EINVAL, "series shorter than L");
-      segs[(size_t)i].n = n[i];
-    }
+    for (int32_t i = 0; i < n_segs; ++i) segs[(size_t)i].n = n[i];
     const bf_search_params prm = {BF_NORM_CENTRED, 1, 1, 0, 0.0, 1.0};
     SearchDev sp = make_search(bank->dev, &prm, MODE_SEARCH);
     fit_tile(bank->dev, segs.data(), n_segs, slots, &sp);
+    int64_t tiles = 0;
     for (int32_t i = 0; i < n_segs; ++i)
       tiles += (n[i] - bank->dev.L + 1 + sp.n_wg - 1) / sp.n_wg;
-    const int32_t r = bank->dev.precision == P_FFT
-                          ? plan_fft_ranges(bank->dev, tiles, slots, sp)
-                          : plan_ranges(bank->dev, tiles, slots, sp.tm, sp.tn);
+    bool split;
+    const int32_t r = plan(bank->dev, sp, tiles, slots, true, &split);
     if (n_ranges) *n_ranges = r;
     if (n_items) *n_items = tiles * r;
   } catch (...) {

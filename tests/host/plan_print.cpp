@@ -1,11 +1,16 @@
 // Prints the work decomposition of FFT searches, one line "<ranges> <items>" per line
 // "<bins> <templates per bin> <L> <blocks of offsets> <CUs> <tails> <t_block>" on stdin (tails: 1
-// for a tail search).  Host code only: the planner needs no device.
+// for a tail search).  Host code only: the planner needs no device.  Exit status 2 if bf_plan
+// does not refuse a series shorter than L by its length, GPU or none.
 #include "bfly_runtime.h"
 
 #include <cstdio>
 
 int main() {
+  bf_bank bank = {};
+  bank.dev.L = 64;
+  const int64_t n[2] = {64, 63};
+  if (bf_plan(&bank, n, 2, nullptr, nullptr) != BF_EINVAL) return 2;
   int n_bins, n_fdot, L, slots, tails, t_block;
   long long blocks;
   while (std::scanf("%d %d %d %lld %d %d %d", &n_bins, &n_fdot, &L, &blocks, &slots, &tails,

@@ -68,3 +68,26 @@ def test_ranges_of_a_long_search(grid):
     assert torch.equal(whole["max_abs"], torch.where(upper, hi["max_abs"], lo["max_abs"]))
     assert torch.equal(whole["argmax"], torch.where(upper, hi["argmax"], lo["argmax"]))
     assert torch.equal(whole["spectrum"], torch.cat([lo["spectrum"], hi["spectrum"]]))
+
+
+@pytest.mark.parametrize("grid,lengths", [((8, 64), [3000]), ((3, 200), [3000, 9001]),
+                                          ((1, 512), [700]), ((9, 97), [9001, 700, 20000]),
+                                          ((1, 2051), [3000]), ((48, 200), [20000])])
+def test_plan_reports_ranges_that_cut_bins(grid, lengths):
+    """bf_plan gives the ranges of the search with default parameters: more than there are bins
+    where they cut bins, a multiple of 8, and the results are those of whole bins (t_block = 4)."""
+    from paper_1802_01685_amd import bfly as bf
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    p = BankParams(fs=600.0, L=600, n_f0=grid[0], n_fdot=grid[1], f0_min=20.0, f0_max=250.0,
+                   fdot_min=-100.0, fdot_max=120.0)
+    xt = [torch.from_numpy(white_noise(n, n).astype(np.float32)).cuda() for n in lengths]
+    bank = bf.bank_create(p, "fft")
+    ranges, items = bf.plan(bank, lengths)
+    assert ranges > grid[0] and ranges % 8 == 0
+    assert items == ranges * sum(-(-(n - p.L + 1) // (8193 - p.L)) for n in lengths)
+    cut = [to_np(o) for o in bf.search_batch(bank, xt, bf.make_params())]
+    whole = [to_np(o) for o in bf.search_batch(bank, xt, bf.make_params(t_block=4))]
+    for a, b in zip(cut, whole):
+        for k in ("max_abs", "argmax", "hist", "spectrum", "n_degenerate"):
+            assert np.array_equal(a[k].view(np.uint8), b[k].view(np.uint8)), k

@@ -74,3 +74,8 @@ def test_tail_plans(plan):
     shapes = [s[:4] + (256, 1, s[4]) for s in TAIL_PLANS]
     got = {s: r for s, (r, _) in zip(TAIL_PLANS, plan(*shapes))}
     assert {s: r for s, r in got.items() if r not in TAIL_PLANS[s]} == {}
+
+
+def test_plan_refuses_short_series_first(plan):
+    """bf_plan's argument checks come before the device is asked for (exit status 2 otherwise)."""
+    assert plan() == []
