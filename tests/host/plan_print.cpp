@@ -1,16 +1,41 @@
 // Prints the work decomposition of FFT searches, one line "<ranges> <items>" per line
 // "<bins> <templates per bin> <L> <blocks of offsets> <CUs> <tails> <t_block>" on stdin (tails: 1
-// for a tail search).  Host code only: the planner needs no device.  Exit status 2 if bf_plan
+// for a tail search).  With an argument, the tile of FP32 searches, "<template blocks> <offset
+// blocks> <offsets per work item>" per line "<bins> <templates per bin> <L> <offsets> <CUs>".
+// Host code only: the planner needs no device.  Exit status 2 if bf_plan
 // does not refuse a series shorter than L by its length, GPU or none.
 #include "bfly_runtime.h"
 
 #include <cstdio>
 
-int main() {
+static void print_tiles() {
+  int n_bins, n_fdot, L, slots;
+  long long W;
+  while (std::scanf("%d %d %d %lld %d", &n_bins, &n_fdot, &L, &W, &slots) == 5) {
+    bfly::BankDev b = {};
+    b.precision = bfly::P_FP32;
+    b.L = L;
+    b.n_bins = n_bins;
+    b.n_fdot = n_fdot;
+    b.K = (int64_t)n_bins * n_fdot;
+    const bf_search_params prm = {BF_NORM_CENTRED, 1, 1, 0, 0.0, 1.0};
+    bfly::SearchDev sp = bfly::make_search(b, &prm);
+    bf_segment seg = {};
+    seg.n = W + L - 1;
+    bfly::fit_tile(b, &seg, 1, slots, &sp);
+    std::printf("%d %d %d\n", sp.tm, sp.tn, sp.n_wg);
+  }
+}
+
+int main(int argc, char**) {
   bf_bank bank = {};
   bank.dev.L = 64;
   const int64_t n[2] = {64, 63};
   if (bf_plan(&bank, n, 2, nullptr, nullptr) != BF_EINVAL) return 2;
+  if (argc > 1) {
+    print_tiles();
+    return 0;
+  }
   int n_bins, n_fdot, L, slots, tails, t_block;
   long long blocks;
   while (std::scanf("%d %d %d %lld %d %d %d", &n_bins, &n_fdot, &L, &blocks, &slots, &tails,

@@ -24,9 +24,9 @@ def plan(tmp_path_factory):
         r = subprocess.run(cmd, capture_output=True, text=True)
         assert r.returncode == 0, r.stderr[-3000:]
 
-    def run(*shapes):
+    def run(*shapes, args=()):
         text = "".join(" ".join(str(v) for v in s) + "\n" for s in shapes)
-        r = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60)
+        r = subprocess.run([exe, *args], input=text, capture_output=True, text=True, timeout=60)
         assert r.returncode == 0, r.stderr[-3000:]
         return [tuple(int(v) for v in line.split()) for line in r.stdout.splitlines()]
 
@@ -79,3 +79,17 @@ def test_tail_plans(plan):
 def test_plan_refuses_short_series_first(plan):
     """bf_plan's argument checks come before the device is asked for (exit status 2 otherwise)."""
     assert plan() == []
+
+
+def test_small_fp32_searches_take_the_small_tile(plan, monkeypatch):
+    """The 1 x 1 tile of 128 offsets up to a few work items per CU (the shapes of
+    test_gpu_small_tile, the shortest among them, whose item counts are those of the 2 x 4 tile),
+    the 2 x 4 tile of 512 beyond and where BF_TILE asks for it."""
+    banks = [(16, 16, 512), (3, 40, 37), (5, 7, 200), (9, 33, 97), (1, 70, 16)]
+    small = [b + (W, 256) for b in banks for W in (1, 127, 128, 129, 513, 1537)]
+    large = [(256, 256, 4096, 126977, 256), (64, 64, 2000, 126001, 256)]
+    monkeypatch.delenv("BF_TILE", raising=False)
+    assert plan(*small, args=("tiles",)) == [(1, 1, 128)] * len(small)
+    assert plan(*large, args=("tiles",)) == [(2, 4, 512)] * len(large)
+    monkeypatch.setenv("BF_TILE", "2x4")
+    assert plan(*small, args=("tiles",)) == [(2, 4, 512)] * len(small)
