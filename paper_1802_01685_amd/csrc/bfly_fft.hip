@@ -914,6 +914,21 @@ __device__ __forceinline__ int lane_here() {
   return l;
 }
 
+// A batch that lists more than PAIRS_MOST of its (block, template) pairs gets the whole tails pass
+// instead, if that pass has work for every CU.  A listed pair takes 1.2 to 2 times as long as one
+// of the whole pass, which sweeps a block's templates in order: with every pair listed 12.4
+// against 9.2 ms at 1000 series x 1024 templates, 22.1 against 17.6 at 150 x 5,874 (66 x 89), and
+// with half of them 2.1 against 2.2 at 150 x 502.
+// With few work items the list is the faster one, 0.83 against 2.24 ms at 64 bins of 512 templates
+// on 2 blocks (128 items).  The batch has one way as a whole: some series by list and some by the
+// pass leave CUs idle in both (200 series x 1024 templates: 3.4 ms where either took 2.3 or 2.4).
+constexpr double PAIRS_MOST = 0.5;
+constexpr int64_t PAIRS_MIN_ITEMS = 512;
+__device__ __forceinline__ bool pairs_too_many(const BatchHdr* hdr, const BankDev& b) {
+  return hdr->n_items >= PAIRS_MIN_ITEMS &&
+         (double)hdr->listed > PAIRS_MOST * (double)b.K * (double)hdr->total_tiles;
+}
+
 template <int SMAX, int MODE>
 __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ hdr, BankDev b,
                                                   SearchDev p) {
@@ -922,7 +937,8 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
   // the tails pass after a single-pass search: most often no series is flagged, and a
   // work-group should not set up its tables to find that out (50 us for 7,680 of them), nor
   // look through the series for a flag (3.6 ms for 8,000 of them with 1,000 series)
-  if (MODE == MODE_TAILS && hdr_segs(hdr)[0].redo && hdr->redo_any == 0u) return;
+  const bool whole = MODE == MODE_TAILS && pairs_too_many(hdr, b);
+  if (MODE == MODE_TAILS && hdr_segs(hdr)[0].redo && hdr->redo_any == 0u && !whole) return;
   constexpr int NO = 2 * SMAX;          // real outputs per thread that can be valid
   __shared__ float2 lds[2 * PADN];
   __shared__ float2 hand[8];            // butterfly 256's first-pass inputs for thread 0
@@ -998,7 +1014,7 @@ __global__ __launch_bounds__(256, 2) void k_fft4k(const BatchHdr* __restrict__ h
     }
     const SegDesc& sg = segs[lo];
     // after a single-pass search the tails pass runs only for flagged series
-    if (MODE == MODE_TAILS && sg.redo && sg.redo[0] == 0u) continue;
+    if (MODE == MODE_TAILS && sg.redo && sg.redo[0] == 0u && !whole) continue;
     const int64_t blk = tt - sg.tile0;
     const int tau_base = (int)(blk * valid);     // series are shorter than 2^31 samples
     const int b_lo = (int)((int64_t)rg * b.n_bins / n_ranges);
@@ -1604,7 +1620,8 @@ __global__ __launch_bounds__(256) void k_bin_sums(const BatchHdr* __restrict__ h
 }
 
 // The tails of the (block, template) pairs the single pass of k_fft4k listed, for every
-// series not flagged (redo = 0; a flagged series gets the full tails pass instead).
+// series not flagged (redo = 0; a flagged series gets the full tails pass instead), unless the
+// batch lists too many.
 // Per pair the transform of k_fft4k with the same operations in the same order, so rho is
 // the same bit for bit, then the compare against kappa sigma_k.  Work unit = a part of the pair
 // list of one (series, shard); a work-group takes its pairs one after another.  Only the shards
@@ -1617,6 +1634,7 @@ template <int SMAX>
 __global__ __launch_bounds__(256, 2) void k_fft4k_pairs(const BatchHdr* __restrict__ hdr,
                                                         BankDev b) {
   using namespace fft4k;
+  if (pairs_too_many(hdr, b)) return;
   constexpr int NO = 2 * SMAX;
   __shared__ float2 lds[2 * PADN];
   __shared__ float2 hand[8];

@@ -165,8 +165,11 @@ struct BatchHdr {
   int64_t n_items;      // total_tiles * n_ranges
   int32_t split;        // 1: ranges of templates that may cut bins (k_fft4k_search only)
   uint32_t redo_any;    // single-pass tail search: 1 once a series has REDO_ALL (0 as uploaded)
-  uint32_t next[8];     // k_fft4k_search with fewer work-groups than items: items taken per XCD
-                        // beyond the first of each work-group (0 in an uploaded table)
+  union {               // (0 in an uploaded table)
+    uint32_t next[8];   // k_fft4k_search with fewer work-groups than items: items taken per XCD
+                        // beyond the first of each work-group
+    unsigned long long listed;   // single-pass tail search, FFT form: pairs listed in all series
+  };
 };
 static_assert(sizeof(BatchHdr) == 64, "BatchHdr layout");
 

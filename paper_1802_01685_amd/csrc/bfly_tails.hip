@@ -169,15 +169,6 @@ __device__ __forceinline__ void flag_all(BatchHdr* hdr, const SegDesc& sg) {
   hdr->redo_any = 1u;
 }
 
-// FFT form: a series that lists more than PAIRS_MOST of its (block, template) pairs gets the whole
-// tails pass instead, if that pass has work for every CU.  A listed pair takes 1.2 to 1.4 times as
-// long as one of the whole pass, which sweeps a block's templates in order: with every pair listed
-// 15.9 against 9.3 ms at 1000 series x 1024 templates, 22.1 against 17.6 at 150 x 5,874 (66 x 89).
-// With few work items the list is the faster one, 0.83 against 2.24 ms at 64 bins of 512 templates
-// on 2 blocks (128 items).
-constexpr double PAIRS_MOST = 0.75;
-constexpr int64_t PAIRS_MIN_ITEMS = 512;
-
 // Per series: REDO_ALL if the candidates of a shard did not fit; direct forms: REDO_TILES if an
 // exact threshold lies below its predicted lower one, with the first bound of each such tile
 // of TILE_K templates overwritten by -1 (bounds are not negative).  One wave per tile.
@@ -189,15 +180,12 @@ __global__ __launch_bounds__(256) void k_tails_check(BatchHdr* __restrict__ hdr,
   if (blockIdx.x == 0 && threadIdx.x < CAND_SHARDS && (int64_t)sg.n_cand[threadIdx.x] > per)
     flag_all(hdr, sg);
   if (b.precision == P_FFT) {   // k_fft_pair_list has listed those templates' blocks
-    if (blockIdx.x == 0 && hdr->n_items >= PAIRS_MIN_ITEMS) {
-      static_assert(CAND_SHARDS == 256, "one thread per shard");
-      __shared__ unsigned int listed;
-      if (threadIdx.x == 0) listed = 0u;
-      __syncthreads();
-      atomicAdd(&listed, (unsigned int)sg.n_cand[threadIdx.x]);
-      __syncthreads();
-      if (threadIdx.x == 0 && (double)listed > PAIRS_MOST * (double)b.K * (double)sg.n_tiles)
-        flag_all(hdr, sg);
+    static_assert(CAND_SHARDS == 256, "one thread per shard");
+    if (blockIdx.x == 0) {
+      unsigned long long n = sg.n_cand[threadIdx.x];
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o, 64);
+      if ((threadIdx.x & 63) == 0 && n) atomicAdd(&hdr->listed, n);
     }
     return;
   }
