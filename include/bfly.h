@@ -243,8 +243,9 @@ bf_status bf_tails_workspace_bytes(const bf_bank* bank, const int64_t* n, int32_
  * the contraction: before it, sigma_k is predicted from the series' own spectrum by
  * Parseval's theorem (Sec. 2.2: the mean square of template k's output is the sum over
  * frequency of |H_k|^2 times the power of the locally normalised series); the pass sums the
- * exact rho^2 per template and keeps every (tau, k) above 0.95 kappa (FFT bank: 0.97 kappa)
- * times the prediction.  A check then selects the tails against the exact kappa * sigma_k;
+ * exact rho^2 per template and keeps every (tau, k) above 0.95 kappa (0.98 kappa up to
+ * kappa = 3; FFT bank: 0.97 kappa) times the prediction.  A check then selects the tails
+ * against the exact kappa * sigma_k;
  * templates whose exact threshold falls below the kept bound get a second pass (an FFT bank
  * transforms their blocks again, the others their tiles of 64 templates), and so does a whole
  * series whose candidate lists overflow.  Results are the same bit for bit as with two

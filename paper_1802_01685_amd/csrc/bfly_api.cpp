@@ -400,8 +400,8 @@ bf_status run_batch(const bf_bank* bank, const bf_segment* segs, int32_t n_segs,
   if (onepass) {
     // BF_TAILS_MARGIN overrides the predicted-threshold margin (a knob; above 1 it makes the
     // check fail, which exercises the fallback)
-    const float margin = (float)env_double(
-        "BF_TAILS_MARGIN", b.precision == P_FFT ? TAILS_MARGIN_FFT : TAILS_MARGIN);
+    const float margin =
+        (float)env_double("BF_TAILS_MARGIN", tails_margin(b.precision, kappa));
     return enqueue_onepass_tail_kernels(bank, sp, sp_t, tab_dev, n_segs, xb, ti.max_n,
                                         ti.n_items, margin, stream, te);
   }

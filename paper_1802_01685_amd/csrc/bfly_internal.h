@@ -226,8 +226,19 @@ enum MainMode { MODE_SEARCH = 0, MODE_SIGMA = 1, MODE_TAILS = 2, MODE_ONEPASS = 
 // of white strain (65,536 x 4096) and 0.986-0.990 on a 64 s light curve and its control, its
 // 1% quantile at 0.975-0.987 on series of 6 to 14 templates' length; a template below the
 // margin costs the FFT form its blocks once more and the direct forms its tile of 64.
+//
+// The direct forms append every kept correlation to a list, which at a low kappa costs more than
+// any tile that has to be run again: 600 templates against 4 x 9,000 samples of bursts at
+// kappa = 3 took 3.51 ms with 0.95 and 3.22 with 0.98, 4,096 against 64,000 28.7 and 26.8; white
+// noise there 0.92 and 0.91, but at kappa = 3.5 0.61 and 0.69.
 constexpr float TAILS_MARGIN = 0.95f;
+constexpr float TAILS_MARGIN_LOW_KAPPA = 0.98f;   // kappa up to TAILS_LOW_KAPPA
+constexpr float TAILS_LOW_KAPPA = 3.0f;
 constexpr float TAILS_MARGIN_FFT = 0.97f;
+inline float tails_margin(int precision, float kappa) {
+  return precision == P_FFT ? TAILS_MARGIN_FFT
+         : kappa <= TAILS_LOW_KAPPA ? TAILS_MARGIN_LOW_KAPPA : TAILS_MARGIN;
+}
 
 // Bytes of the quantised templates, of the per-template side tables, and of the whole bank
 // allocation (templates, side tables, then a 256-byte status word).
