@@ -1626,9 +1626,9 @@ __global__ __launch_bounds__(256) void k_bin_sums(const BatchHdr* __restrict__ h
 // the same bit for bit, then the compare against kappa sigma_k.  Work unit = a part of the pair
 // list of one (series, shard); a work-group takes its pairs one after another.  Only the shards
 // that hold templates count (64 templates each at least), a list has parts where there are fewer
-// lists than work-groups, and the work-groups take lists of different series, so that lists as
-// long as the bank (templates below their bound) do not fall to a few work-groups.  Two work-groups
-// per CU: within 256 registers only the block change (a few times per shard) reloads spilled
+// lists than work-groups, so that lists as long
+// as the bank (templates below their bound) do not fall to a few work-groups.  Two work-groups per
+// CU: within 256 registers only the block change (a few times per shard) reloads spilled
 // values.
 template <int SMAX>
 __global__ __launch_bounds__(256, 2) void k_fft4k_pairs(const BatchHdr* __restrict__ hdr,
@@ -1676,19 +1676,26 @@ __global__ __launch_bounds__(256, 2) void k_fft4k_pairs(const BatchHdr* __restri
   const int n_lists = hdr->n_segs * n_shards;
   const int parts = max((int)gridDim.x / n_lists, 1);
   for (int unit = blockIdx.x; unit < n_lists * parts; unit += gridDim.x) {
-    const int shard = unit % n_lists / hdr->n_segs;
-    const SegDesc& sg = segs[(unit % hdr->n_segs + 37 * shard) % hdr->n_segs];
+    // A small bank's templates below their bound lie together in few shards, so each shard is dealt
+    // over all series before the next; a large bank's lie in all, and its lists go series by
+    // series, at 8 shards further on each, so that an XCD's lists share spectra in its L2.
+    const int list = unit % n_lists;
+    const bool large = n_shards >= 64;
+    const int shard0 = large ? list % n_shards : list / hdr->n_segs;
+    const int seg = large ? list / n_shards : (list % hdr->n_segs + 37 * shard0) % hdr->n_segs;
+    const int shard = large ? (shard0 + 8 * seg) % n_shards : shard0;
+    const SegDesc& sg = segs[seg];
     if (!sg.redo || sg.redo[0] != 0u || !sg.c_tau) continue;
-    const int64_t per = sg.cand_cap / CAND_SHARDS;
-    const int64_t listed = min((int64_t)sg.n_cand[shard], per);
-    const int64_t j_lo = listed * (unit / n_lists) / parts;
-    const int64_t n = listed * (unit / n_lists + 1) / parts;
+    const int per = (int)(sg.cand_cap / CAND_SHARDS);   // at most 2^16
+    const int listed = (int)min(sg.n_cand[shard], (unsigned long long)per);
+    const int j_lo = (int)((int64_t)listed * (unit / n_lists) / parts);
+    const int n = (int)((int64_t)listed * (unit / n_lists + 1) / parts);
     if (j_lo >= n) continue;
     // A shard's pairs come in runs of one block (a work-group appends the pairs of its
     // current block), so the block's spectrum and scales are reloaded only when the block
     // changes; the next pair's template spectrum is loaded while the current one transforms.
-    const int64_t e0 = shard * per;
-    int64_t blk_n = sg.c_tau[e0 + j_lo];
+    const int e0 = shard * per;
+    int blk_n = sg.c_tau[e0 + j_lo];
     int k_n = sg.c_k[e0 + j_lo];
     float2 ha[8], hb[8], hha, hhb;
     auto load_h = [&](int k) {
@@ -1702,12 +1709,12 @@ __global__ __launch_bounds__(256, 2) void k_fft4k_pairs(const BatchHdr* __restri
       hhb = row_load(hr, 8u * (unsigned)(M - ha_idx), 0u);
     };
     load_h(k_n);
-    int64_t cur_blk = -1;
+    int cur_blk = -1;
     int tau_base = 0;
     float2 xa[8], xb[8];
     float sinv[NO];
-    for (int64_t j = j_lo; j < n; ++j, ++it) {
-      const int64_t blk = blk_n;
+    for (int j = j_lo; j < n; ++j, ++it) {
+      const int blk = blk_n;
       const int k = k_n;
       if (blk != cur_blk) {
         cur_blk = blk;
