@@ -245,11 +245,11 @@ bf_status bf_tails_workspace_bytes(const bf_bank* bank, const int64_t* n, int32_
  * frequency of |H_k|^2 times the power of the locally normalised series); the pass sums the
  * exact rho^2 per template and keeps every (tau, k) above 0.95 kappa (0.98 kappa up to
  * kappa = 3; FFT bank: 0.97 kappa) times the prediction.  A check then selects the tails
- * against the exact kappa * sigma_k;
- * templates whose exact threshold falls below the kept bound get a second pass (an FFT bank
- * transforms their blocks again, the others their tiles of 64 templates), and so does a whole
- * series whose candidate lists overflow.  Results are the same bit for bit as with two
- * passes (sums first, extraction second).  With an FFT bank of N < 8192 points the search,
+ * against the exact kappa * sigma_k; templates whose exact threshold falls below the kept
+ * bound get a second pass (an FFT bank transforms their blocks again, the others their tiles
+ * of 64 templates), and so does a whole series whose candidate lists overflow, or a whole
+ * batch in which most of an FFT bank's blocks would be transformed again.  Results are the
+ * same bit for bit as with two passes (sums first, extraction second).  With an FFT bank of N < 8192 points the search,
  * the sums and the extraction are three passes of the FFT kernel.  kappa finite and >= 0;
  * sigma, bin_counts and n_tails are required.  segs is a host array. */
 bf_status bf_search_tails(const bf_bank* bank, const bf_tail_segment* segs, int32_t n_segs,

@@ -67,7 +67,8 @@ constexpr int chunk_taps(int precision) {
 }
 // Work-groups of k_main a CU holds, by form and offset blocks per wave: FP8's 2 x 4 tile fits
 // twice (128 accumulators and one strip-fragment buffer in 256 registers, 20 KB of LDS at
-// L = 2000).
+// L = 2000), in the tail modes too, at 104 and 108 B of scratch per lane: the tails of 128,000
+// samples against 16,384 templates take 3.8 ms (5.4 with one and without that scratch).
 constexpr int main_wgs_per_cu(int precision, int tn) {
   return precision == P_FP8 && tn <= 4 ? 2 : 1;
 }
@@ -293,13 +294,14 @@ bool fft_can_split_bins(const BankDev& b, const SearchDev& p);
 // The sigma or tails pass of a tail search (p.mode), after the search left the data spectra.
 // Single-pass tail search (bfly_tails.hip, bfly_fft.hip).  The predictor: lag sums of each
 // series' locally normalised samples (k_acf), their cosine transform on pred_n points
-// (k_qspec), and per template kappa * margin * sqrt(sum_f |H_k(f)|^2 Q(f) / (n_ok pred_n))
+// (k_qspec), and per template kappa * margin * sqrt(sum_f |H_k(f)|^2 Q(f) / (n_ok pred_n) W / n)
 // from the bank's spectra (FFT form) or from spectra made on the fly (direct forms).  After
 // the pass that sums rho^2 and keeps candidates above those thresholds: k_tails_check flags
 // a series whose candidates overflowed (direct forms: and the template tiles whose exact
 // thresholds fall below the predicted ones), and k_tails_keep (direct forms) moves the other
 // candidates above the exact thresholds into the tail lists, or launch_fft_pairs (FFT form)
-// transforms the listed pairs again; the tails pass then runs only for what is flagged.
+// transforms the listed pairs again; the tails pass then runs only for what is flagged, or for all
+// of an FFT batch that lists too many pairs.
 int pred_points(const BankDev& b);
 // The FFT form's search kernel has the single-pass mode (N = 8192, fewer than 2^16
 // templates per f0 bin).  Its candidates are (block, template) pairs, not correlations: the

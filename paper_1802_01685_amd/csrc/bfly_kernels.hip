@@ -283,9 +283,9 @@ hipError_t launch_bank_gen(const GridDev& g, const BankDev& b, void* dst, hipStr
 // separately), in two launches: k_zero also sums every chunk of PRE_CHUNK samples, and k_prefix
 // adds the chunks before its own and scans within it, so every CU takes part (one work-group
 // per series scanning chunk after chunk took 15 us for 2,048 samples, 186 us for 65,536 and
-// 1.1 ms for 397,311; now 7.5 us for 2,048 and 10 us for 65,536).  Bound by latency.  The sums of float samples and of their squares are exact in
-// double-double unless the samples span more than about 2^20 in magnitude, so the order of
-// the additions does not show.  The chunk sums live in the running-maxima buffer until
+// 1.1 ms for 397,311; now 7.5 us for 2,048 and 10 us for 65,536).  Bound by latency.  The sums of
+// float samples and of their squares are exact in double-double unless the samples span more than
+// about 2^20 in magnitude, so the order of the additions does not show.  The chunk sums live in the running-maxima buffer until
 // k_norms clears it: 40 bytes per 2,048 samples of a series of W + L - 1 fit its
 // round_up(8 W, 256) bytes for every L <= 8192.
 // ---------------------------------------------------------------------------------------

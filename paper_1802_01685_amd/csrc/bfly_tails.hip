@@ -14,8 +14,8 @@
 // predicted one and the candidates fit.  Templates for which the first fails are handled by
 // themselves: the FFT form lists all their blocks for the second transform, the direct forms
 // run the ordinary tails pass over the template tiles that hold one; a series whose candidates
-// did not fit gets the whole pass.  Either way the tails, sigma and counts are those of the
-// two-pass search, bit for bit.
+// did not fit gets the whole pass, and so does an FFT batch that lists most of its pairs.  Either
+// way the tails, sigma and counts are those of the two-pass search, bit for bit.
 #include "bfly_internal.h"
 
 #include <hip/hip_runtime.h>
