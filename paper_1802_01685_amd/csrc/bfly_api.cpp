@@ -648,8 +648,7 @@ int32_t plan_split_ranges(const BankDev& b, int64_t total_tiles, int slots, int3
 }
 
 constexpr int XCDS = 8;
-int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, int tn,
-                    double* makespan) {
+int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, int tn) {
   double best_cost = 1e300;
   int32_t best_r = 1;
   const int64_t conc = (int64_t)slots * main_wgs_per_cu(b.precision, tn);
@@ -670,18 +669,41 @@ int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, in
     }
     if (items > 64LL * conc) break;
   }
-  if (makespan) *makespan = best_cost;
   return best_r;
 }
 
+// Time of an FP32 search in k_main, in us, on the 1 x 1 or the 2 x 4 tile.  Per round of work
+// items (two 1 x 1 items run on a CU at once): a start, the ends of the bins, and per template
+// tile its epilogue and its K-loop; the 1 x 1 tile no faster than its MFMAs (16.8 ns a tap and
+// tile) item after item.  Then the spectrum sums: each wave adds one word per bin, 13.3 ns each on the 8 words of
+// a cache line, whoever adds them, and the 1 x 1 tile has four times the waves.  Fitted to 680
+// searches (L from 37 to 4096, 20 to 34,812 templates, 60 to 200,000 offsets).
+double fp32_us(const BankDev& b, int m, int64_t items, int32_t ranges, int64_t offsets, int slots) {
+  const int64_t g = 32 * m, bins = (b.n_bins + ranges - 1) / ranges;
+  const int64_t whole = (b.K + g - 1) / g;       // tiles of the bank
+  const bool aligned = ranges == 1 || b.n_fdot % g == 0;
+  const double most = (double)std::min(whole, (bins * b.n_fdot + g - 1) / g + (aligned ? 0 : 1));
+  const double words = (double)offsets * std::min(b.n_bins, 8) * 1e-3;
+  if (m == 1) {
+    const double rounds = (double)((items + 2 * slots - 1) / (2 * slots));
+    const double start_to_end = rounds * (7.0 + 0.9 * bins + most * (0.77 + 0.017 * b.L_pad));
+    const double mfma = (double)((items + slots - 1) / slots) * most * (0.2 + 0.0168 * b.L_pad);
+    return std::max(start_to_end, mfma) + 0.42 * words;
+  }
+  const double rounds = (double)((items + slots - 1) / slots);
+  return rounds * (3.62 * bins + most * (1.94 + 0.112 * b.L_pad)) + 0.061 * words + 8.2;
+}
+
 // A search too small for the default tile: FP32's 1 x 1 tile (128 offsets per work-group, 32
-// templates at a time) where it shortens the longest CU's work, in accumulator blocks, by a
-// tenth or more.  At 4 s of 512 Hz against a 16 x 16 bank the 2 x 4 tile makes 32 work items of
-// one 64-template tile each and the search takes 75 us in k_main, a quarter of the chip one
-// block after another; the 1 x 1 tile makes 104 items an eighth as long (20 us).  From a few
-// items per CU on the two tie and the 2 x 4 tile, which reads each fragment fewer times, stays.
-// The results do not depend on the shape in FP32.  (The other forms' strips carry scales or
-// schedules tied to their tile and stay as they are.)
+// templates at a time) where it takes less time by fp32_us.  At 4 s of 512 Hz against a 16 x 16
+// bank the 2 x 4 tile makes 32 work items of one 64-template tile each and the search takes 75 us
+// in k_main, a quarter of the chip one block after another; the 1 x 1 tile makes 104 items an
+// eighth as long (20 us).  On long series and short templates the 2 x 4 tile wins by its fewer
+// spectrum sums: 133,760 offsets against 36 x 3 templates of 64 taps 0.38 and 0.85 ms, 200,000
+// against 4 x 8 0.11 and 0.31.  Over the 680 searches the choice is 0.4% behind the faster tile on
+// average and at most 3% behind the 2 x 4 tile.  The results do not depend on the shape in
+// FP32.  (The other forms' strips carry scales or schedules tied to their tile and stay as they
+// are.)
 void fit_tile(const BankDev& b, const bf_segment* segs, int32_t n_segs, int slots,
               SearchDev* sp) {
   int32_t tm, tn, pipe;
@@ -690,13 +712,16 @@ void fit_tile(const BankDev& b, const bf_segment* segs, int32_t n_segs, int slot
     return;
   const auto cost = [&](int m, int n) {
     const int64_t n_wg = 32 * n * WG_WAVES;
-    int64_t tiles = 0;
-    for (int32_t i = 0; i < n_segs; ++i) tiles += (segs[i].n - b.L + 1 + n_wg - 1) / n_wg;
-    double c = 0.0;
-    plan_ranges(b, tiles, slots, m, n, &c);
-    return c * m * n;
+    int64_t tiles = 0, offsets = 0;
+    for (int32_t i = 0; i < n_segs; ++i) {
+      const int64_t W = segs[i].n - b.L + 1;
+      tiles += (W + n_wg - 1) / n_wg;
+      offsets += W;
+    }
+    const int32_t r = plan_ranges(b, tiles, slots, m, n);
+    return fp32_us(b, m, tiles * r, r, offsets, slots);
   };
-  if (cost(1, 1) < 0.9 * cost(sp->tm, sp->tn)) {
+  if (cost(1, 1) < cost(sp->tm, sp->tn)) {
     sp->tm = sp->tn = 1;
     sp->n_wg = 32 * WG_WAVES;
   }

@@ -75,9 +75,7 @@ bf_status check_params(const bf_search_params* p);
 SearchDev make_search(const BankDev& b, const bf_search_params* p, int mode = MODE_SEARCH,
                       float kappa = 0.0f);
 bf_status device_slots(int* slots);
-// makespan (may be null): the plan's estimated longest work per CU, in tiles.
-int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, int tn,
-                    double* makespan = nullptr);
+int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, int tn);
 // Changes the default tile where the series are too small for it (never one chosen by BF_TILE).
 void fit_tile(const BankDev& b, const bf_segment* segs, int32_t n_segs, int slots,
               SearchDev* sp);

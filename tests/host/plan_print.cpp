@@ -18,6 +18,7 @@ static void print_tiles() {
     b.n_bins = n_bins;
     b.n_fdot = n_fdot;
     b.K = (int64_t)n_bins * n_fdot;
+    b.L_pad = (L + 31) / 32 * 32;
     const bf_search_params prm = {BF_NORM_CENTRED, 1, 1, 0, 0.0, 1.0};
     bfly::SearchDev sp = bfly::make_search(b, &prm);
     bf_segment seg = {};
