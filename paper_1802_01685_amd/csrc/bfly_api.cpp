@@ -625,22 +625,28 @@ int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots, const 
 // Ranges of whole bins leave CUs idle when a search has few of them.  k_fft4k_search also takes
 // ranges of templates that cut bins: a multiple of 8, so that each XCD sweeps its own ranges in
 // step and shares their spectra through its L2, as many as fill the XCD's 64 work-groups q
-// times.  Taken where fft4k_cost falls by a twentieth and by k_bin_sums' 15 us, about 5
-// templates.  7 blocks against 48 bins of 200 templates: 336 items of 200 templates or 504 of
-// 133, 0.71 and 0.50 ms in the kernel (1.09 and 0.88 ms for the search and its bank).  Returns
-// the ranges, 0 for whole bins.
-int32_t plan_split_ranges(const BankDev& b, int64_t total_tiles, int slots, int32_t n_ranges) {
+// times.  In us: 2 a template of fft4k_cost, k_bin_sums' 10, and the parts of bins that meet in
+// atomics, on the spectrogram and once more on the maxima for each range, 9 ps an offset and part
+// (a whole bin stores its row).  Taken where that is a twentieth less.  7 blocks against 48 bins
+// of 200 templates: 336 items of 200 templates or 504 of 133, 0.71 and 0.50 ms in the kernel (1.09
+// and 0.88 ms for the search and its bank); but 3 blocks against 64 bins of 16 0.115 and 0.173 ms,
+// one against 255 of 4 0.100 and 0.140.  Over 136 searches of 1 to 6 blocks the choice is 0.3%
+// behind the best of the counts here and behind whole bins in none.  Returns the ranges, 0 for
+// whole bins.
+int32_t plan_split_ranges(const BankDev& b, int64_t total_tiles, int64_t offsets, int slots,
+                          int32_t n_ranges) {
   const int64_t per_xcd = 2 * (int64_t)slots / 8;
   const double whole = fft4k_cost((total_tiles * n_ranges + 7) / 8, per_xcd,
                                   (int64_t)((b.n_bins + n_ranges - 1) / n_ranges) * b.n_fdot);
   int32_t best = 0;
-  double best_cost = 0.95 * whole - 5.0;
+  double best_us = 0.95 * 2.0 * whole;
   for (int q = 1; q <= 4; ++q) {
     const int64_t r = 8 * (q * per_xcd / total_tiles);
     if (r < 8 || r > b.K) continue;
-    const double c = fft4k_cost(total_tiles * (r / 8), per_xcd, (b.K + r - 1) / r);
-    if (c < best_cost) {
-      best_cost = c;
+    const double us = 2.0 * fft4k_cost(total_tiles * (r / 8), per_xcd, (b.K + r - 1) / r) + 10.0 +
+                      9e-6 * (double)offsets * (double)(b.n_bins + 2 * r);
+    if (us < best_us) {
+      best_us = us;
       best = (int32_t)r;
     }
   }
@@ -728,13 +734,13 @@ void fit_tile(const BankDev& b, const bf_segment* segs, int32_t n_segs, int slot
 }
 
 // The ranges of a search.  *split: they may cut bins (where may_split allows it).
-static int32_t plan(const BankDev& b, const SearchDev& sp, int64_t total_tiles, int slots,
-                    bool may_split, bool* split) {
+static int32_t plan(const BankDev& b, const SearchDev& sp, int64_t total_tiles, int64_t offsets,
+                    int slots, bool may_split, bool* split) {
   *split = false;
   if (b.precision != P_FFT) return plan_ranges(b, total_tiles, slots, sp.tm, sp.tn);
   const int32_t whole = plan_fft_ranges(b, total_tiles, slots, sp);
   if (!may_split || !fft_can_split_bins(b, sp)) return whole;
-  const int32_t cut = plan_split_ranges(b, total_tiles, slots, whole);
+  const int32_t cut = plan_split_ranges(b, total_tiles, offsets, slots, whole);
   *split = cut > 0;
   return cut > 0 ? cut : whole;
 }
@@ -744,7 +750,7 @@ TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s,
   TableInfo ti;
   bool all_spec = true;
   SegDesc* tab = (SegDesc*)(hdr + 1);
-  int64_t tiles = 0;
+  int64_t tiles = 0, offsets = 0;
   for (int32_t i = 0; i < n; ++i) {
     SegDesc& d = tab[i];
     d.x = s[i].x;
@@ -753,6 +759,7 @@ TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s,
     d.n_tiles = (d.W + sp.n_wg - 1) / sp.n_wg;
     d.tile0 = tiles;
     tiles += d.n_tiles;
+    offsets += d.W;
     d.pre = s[i].pre;
     d.cnt = s[i].cnt;
     d.inv_norm = s[i].inv_norm;
@@ -799,7 +806,7 @@ TableInfo fill_table(const BankDev& b, const SearchDev& sp, const SeriesBufs* s,
   std::memset(hdr, 0, sizeof(BatchHdr));
   hdr->n_segs = n;
   hdr->total_tiles = tiles;
-  hdr->n_ranges = plan(b, sp, tiles, slots, may_split && all_spec, &ti.split);
+  hdr->n_ranges = plan(b, sp, tiles, offsets, slots, may_split && all_spec, &ti.split);
   hdr->split = ti.split;
   hdr->n_items = tiles * hdr->n_ranges;
   ti.n_items = hdr->n_items;
@@ -1208,11 +1215,14 @@ bf_status bf_plan(const bf_bank* bank, const int64_t* n, int32_t n_segs, int32_t
     const bf_search_params prm = {BF_NORM_CENTRED, 1, 1, 0, 0.0, 1.0};
     SearchDev sp = make_search(bank->dev, &prm, MODE_SEARCH);
     fit_tile(bank->dev, segs.data(), n_segs, slots, &sp);
-    int64_t tiles = 0;
-    for (int32_t i = 0; i < n_segs; ++i)
-      tiles += (n[i] - bank->dev.L + 1 + sp.n_wg - 1) / sp.n_wg;
+    int64_t tiles = 0, offsets = 0;
+    for (int32_t i = 0; i < n_segs; ++i) {
+      const int64_t W = n[i] - bank->dev.L + 1;
+      tiles += (W + sp.n_wg - 1) / sp.n_wg;
+      offsets += W;
+    }
     bool split;
-    const int32_t r = plan(bank->dev, sp, tiles, slots, true, &split);
+    const int32_t r = plan(bank->dev, sp, tiles, offsets, slots, true, &split);
     if (n_ranges) *n_ranges = r;
     if (n_items) *n_items = tiles * r;
   } catch (...) {

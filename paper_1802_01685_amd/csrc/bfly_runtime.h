@@ -81,6 +81,9 @@ void fit_tile(const BankDev& b, const bf_segment* segs, int32_t n_segs, int slot
               SearchDev* sp);
 // The plan depends on the search's mode (a tail search's kernel has another cost) and t_block.
 int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots, const SearchDev& sp);
+// Ranges that cut bins in place of n_ranges ranges of whole bins; 0: keep those.
+int32_t plan_split_ranges(const BankDev& b, int64_t total_tiles, int64_t offsets, int slots,
+                          int32_t n_ranges);
 // FFT form: overlap-save blocks of a series with W offsets.
 inline int64_t fft_blocks(const BankDev& b, int64_t W) {
   const int64_t v = 2 * (int64_t)b.fft_m - b.L + 1;

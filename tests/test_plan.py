@@ -97,3 +97,18 @@ def test_small_fp32_searches_take_the_small_tile(plan, monkeypatch):
     assert plan(*large, args=("tiles",)) == [(2, 4, 512)] * len(large)
     monkeypatch.setenv("BF_TILE", "2x4")
     assert plan(*small, args=("tiles",)) == [(2, 4, 512)] * len(small)
+
+
+def test_ranges_cut_bins_where_that_is_faster(plan):
+    """Searches of one series on an MI355X in which ranges that cut bins took at least 1.1 times as
+    long as whole bins (their parts of bins meet in atomics), and in which
+    they took at most 0.8 times as long."""
+    # bins, templates per bin, L, offsets, CUs
+    slower = [(255, 4, 512, 4373), (64, 16, 512, 4373), (510, 2, 2000, 7001), (64, 16, 600, 19401),
+              (100, 10, 600, 19401), (60, 9, 600, 19401), (300, 16, 1024, 38977),
+              (700, 3, 1024, 38977), (600, 1, 1024, 38977)]
+    faster = [(9, 97, 512, 4373), (5, 300, 600, 19401), (1, 600, 2000, 7001), (48, 200, 4096, 28673),
+              (16, 64, 2000, 7001), (40, 100, 512, 4373)]
+    cuts = [r[0] for r in plan(*[s + (256,) for s in slower + faster], args=("cuts",))]
+    assert cuts[:len(slower)] == [0] * len(slower)
+    assert all(c > s[0] for c, s in zip(cuts[len(slower):], faster))
