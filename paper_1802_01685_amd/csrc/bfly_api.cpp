@@ -543,18 +543,17 @@ bf_status device_slots(int* slots) {
 // waves: estimated makespan = ceil(items / slots) * (tiles of the largest range), plus a
 // small per-item cost (strip fill and flushes).  With at least 8 bins the count is a
 // multiple of 8, so that each XCD sweeps its own ranges (see the item order in k_main).
-// FFT form: items = blocks x ranges of whole f0 bins; two work-groups fit a CU.  Minimises
-// waves x (bins per range), preferring fewer ranges (each item transforms its block once).
-// The N = 8192 kernel deals each XCD whole ranges when their count is a multiple of 8, so its
-// plan counts one XCD's items on its 64 work-groups.
-//
-// Cost of a plan of k_fft4k_search in templates: an item's set-up and bin end take
-// about as long as 6 templates, and of two work-groups on a CU the older one's waves win the
-// issue slots (2.65 against 3.8 us per template), so the younger one's last item runs on alone:
-// about 0.3 of an item where work-groups take several, 0.1 in a single round.  Short items
-// therefore pay until their set-up shows: 65,536 x 4096 on 31 blocks takes 12.6 ms with 16
-// ranges, 11.9 with 128 and 11.3 with 256; 720,000 x 2000 on 42 blocks 178 ms with 24 and
-// 170 ms with 240.
+// FFT form: items = blocks x ranges of whole f0 bins; two work-groups fit a CU.  The N = 8192
+// kernels deal each XCD whole ranges when their count is a multiple of 8, so their plan counts one
+// XCD's items on its 64 work-groups: whole rounds of the largest item, whose length in templates
+// has 3 for its set-up, and for each bin's end 1, or 16 where its row is decimated (atomics of 64
+// lanes on one word).  Of plans within 2%, the one of the shortest items: of two work-groups on a CU
+// the older one's waves win the issue slots (2.65 against 3.8 us per template in the search), and
+// long items leave the younger one's last running on alone.  65,536 x 4096 on 31 blocks takes
+// 12.6 ms with 16 ranges, 11.9 with 128 and 11.3 with 256; 720,000 x 2000 on 42 blocks 178 ms with
+// 24 and 170 ms with 240; 14 blocks against 200 bins of 10 0.49 ms with 80 and 0.39 with 72, a
+// whole number of rounds.  Over 34 searches the choice is on average 1.2% behind the best of the
+// multiples of 8 up to 512, by rounds of bins alone 1.9%; over 43 tail searches 2.5% and 3.8%.
 //
 // Within a long item the work-groups of an XCD drift apart, the older ones ahead, and no longer
 // read the same spectra out of the caches: about 2% for each doubling past DRIFT templates (128
@@ -562,49 +561,31 @@ bf_status device_slots(int* slots) {
 // longer: 84 series against 512 bins of 512 templates take 5.9 s with 8 or 16 ranges, 5.7 with
 // 32, 5.5 with 64 and 5.6 with 128 or 256.
 constexpr int64_t DRIFT = 4096;
-double fft4k_cost(int64_t items_per_xcd, int64_t per_xcd, int64_t templates) {
-  const double len = (double)templates, n = (double)items_per_xcd;
-  if (items_per_xcd <= per_xcd) return 1.1 * len + 6.0;
-  const double drift = templates > DRIFT ? 1.0 + 0.02 * std::log2(len / DRIFT) : 1.0;
-  return n * (len + 6.0) / (double)per_xcd * drift + 0.3 * len;
+double drift(int64_t templates) {
+  return templates > DRIFT ? 1.0 + 0.02 * std::log2((double)templates / DRIFT) : 1.0;
 }
 
 // A launch has a work-group per item, of up to 512 threads (k_fft_data, k_fft4k_search), and HIP
 // takes fewer than 2^32 threads: 240 ranges of a 240 x 3000 bank on 35,000 blocks would be refused.
 constexpr int64_t MAX_FFT_ITEMS = (((int64_t)1 << 32) - 1) / 512;
 
-// k_fft4k (a tail search's passes) has two waves on a SIMD instead of four and shares a CU more
-// evenly: its time goes by whole rounds of the largest item, with about 4 templates of set-up, and
-// 8 for each bin's end into decimated spectrogram rows (atomics).  Of plans within 3%, the one of
-// the shortest items.  By fft4k_cost 200 blocks against 16 bins of 64 templates took 2.67 ms on 8
-// ranges, this rule's 16 take 2.37; 100 against 300 of 5 4.34 and 4.03; 40 against 201 templates
-// with t_block = 16 0.60 and 0.55.  Over 43 such shapes its choice is on average 2.5% behind the
-// best of the multiples of 8 up to 512, by fft4k_cost 7.2% and by rounds of bins alone 3.6%.  The
-// tails of a 64 s light curve against 60 bins of 3,000 templates take 40.9 ms instead of 50.8.
-double fft4k_rounds(int64_t items_per_xcd, int64_t per_xcd, int64_t bins, int64_t n_fdot,
-                    bool decimated) {
-  return (double)((items_per_xcd + per_xcd - 1) / per_xcd) *
-         ((double)(bins * (n_fdot + (decimated ? 8 : 0))) + 4.0);
-}
-
 int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots, const SearchDev& sp) {
   double best_cost = 1e300;
   int32_t best_r = 1;
-  const int64_t conc = 2 * (int64_t)slots;
-  const bool search = sp.mode == MODE_SEARCH;
+  const int64_t conc = 2 * (int64_t)slots, per_xcd = std::max<int64_t>(conc / 8, 1);
   if (b.fft_m == 4096 && b.n_bins >= 8) {
+    const int64_t bin = b.n_fdot + (sp.t_block > 1 ? 16 : 1);
     for (int32_t r = 8; r <= b.n_bins; r += 8) {
       const int64_t items = total_tiles * r;
       if (items > MAX_FFT_ITEMS) break;
-      const int64_t bins = (b.n_bins + r - 1) / r, templates = bins * b.n_fdot;
-      const double cost =
-          search ? fft4k_cost(total_tiles * (r / 8), conc / 8, templates)
-                 : fft4k_rounds(total_tiles * (r / 8), conc / 8, bins, b.n_fdot, sp.t_block > 1);
-      if (cost < best_cost * (search ? 0.999 : 1.03)) {
+      const int64_t bins = (b.n_bins + r - 1) / r;
+      const int64_t rounds = (total_tiles * (r / 8) + per_xcd - 1) / per_xcd;
+      const double cost = (double)(rounds * (bins * bin + 3)) * drift(bins * b.n_fdot);
+      if (cost < 1.02 * best_cost) {
         best_cost = std::min(best_cost, cost);
         best_r = r;
       }
-      if (items > 64 * conc && templates <= DRIFT) break;
+      if (items > 64 * conc && bins * b.n_fdot <= DRIFT) break;
     }
     return best_r;
   }
@@ -620,6 +601,14 @@ int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots, const 
     if (items > 16 * conc) break;
   }
   return best_r;
+}
+
+// Length of a plan of k_fft4k_search in templates: an item's set-up and bin ends count as 6, and
+// the last item's end alone on its CU as 0.3 of it, 0.1 in a single round.
+double fft4k_cost(int64_t items_per_xcd, int64_t per_xcd, int64_t templates) {
+  const double len = (double)templates, n = (double)items_per_xcd;
+  if (items_per_xcd <= per_xcd) return 1.1 * len + 6.0;
+  return n * (len + 6.0) / (double)per_xcd * drift(templates) + 0.3 * len;
 }
 
 // Ranges of whole bins leave CUs idle when a search has few of them.  k_fft4k_search also takes
@@ -681,9 +670,9 @@ int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, in
 // Time of an FP32 search in k_main, in us, on the 1 x 1 or the 2 x 4 tile.  Per round of work
 // items (two 1 x 1 items run on a CU at once): a start, the ends of the bins, and per template
 // tile its epilogue and its K-loop; the 1 x 1 tile no faster than its MFMAs (16.8 ns a tap and
-// tile) item after item.  Then the spectrum sums: each wave adds one word per bin, 13.3 ns each on the 8 words of
-// a cache line, whoever adds them, and the 1 x 1 tile has four times the waves.  Fitted to 680
-// searches (L from 37 to 4096, 20 to 34,812 templates, 60 to 200,000 offsets).
+// tile) item after item.  Then the spectrum sums: each wave adds one word per bin, 13.3 ns each on
+// the 8 words of a cache line, whoever adds them, and the 1 x 1 tile has four times the waves.
+// Fitted to 680 searches (L from 37 to 4096, 20 to 34,812 templates, 60 to 200,000 offsets).
 double fp32_us(const BankDev& b, int m, int64_t items, int32_t ranges, int64_t offsets, int slots) {
   const int64_t g = 32 * m, bins = (b.n_bins + ranges - 1) / ranges;
   const int64_t whole = (b.K + g - 1) / g;       // tiles of the bank

@@ -79,7 +79,7 @@ int32_t plan_ranges(const BankDev& b, int64_t total_tiles, int slots, int tm, in
 // Changes the default tile where the series are too small for it (never one chosen by BF_TILE).
 void fit_tile(const BankDev& b, const bf_segment* segs, int32_t n_segs, int slots,
               SearchDev* sp);
-// The plan depends on the search's mode (a tail search's kernel has another cost) and t_block.
+// sp: the plan depends on t_block.
 int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots, const SearchDev& sp);
 // Ranges that cut bins in place of n_ranges ranges of whole bins; 0: keep those.
 int32_t plan_split_ranges(const BankDev& b, int64_t total_tiles, int64_t offsets, int slots,

@@ -70,10 +70,24 @@ TAIL_PLANS = {
 }
 
 
-def test_tail_plans(plan):
-    shapes = [s[:4] + (256, 1, s[4]) for s in TAIL_PLANS]
-    got = {s: r for s, (r, _) in zip(TAIL_PLANS, plan(*shapes))}
-    assert {s: r for s, r in got.items() if r not in TAIL_PLANS[s]} == {}
+# the same in plain searches
+SEARCH_PLANS = {
+    (200, 10, 1024, 14, 1): {72},
+    (200, 10, 1024, 14, 16): {72},
+    (16, 64, 600, 200, 1): {16},
+    (96, 3, 512, 40, 1): {24, 32},
+    (64, 30, 2000, 40, 256): {64},
+    (128, 40, 4096, 28, 1): {64, 128},
+    (256, 256, 4096, 31, 1): {256},
+    (240, 3000, 2000, 42, 1): {48, 240},
+}
+
+
+@pytest.mark.parametrize("tails", [0, 1])
+def test_plans_near_the_fastest(plan, tails):
+    fastest = TAIL_PLANS if tails else SEARCH_PLANS
+    got = {s: r for s, (r, _) in zip(fastest, plan(*[s[:4] + (256, tails, s[4]) for s in fastest]))}
+    assert {s: r for s, r in got.items() if r not in fastest[s]} == {}
 
 
 def test_plan_refuses_short_series_first(plan):
