@@ -552,8 +552,8 @@ bf_status device_slots(int* slots) {
 // long items leave the younger one's last running on alone.  65,536 x 4096 on 31 blocks takes
 // 12.6 ms with 16 ranges, 11.9 with 128 and 11.3 with 256; 720,000 x 2000 on 42 blocks 178 ms with
 // 24 and 170 ms with 240; 14 blocks against 200 bins of 10 0.49 ms with 80 and 0.39 with 72, a
-// whole number of rounds.  Over 34 searches the choice is on average 1.2% behind the best of the
-// multiples of 8 up to 512, by rounds of bins alone 1.9%; over 43 tail searches 2.5% and 3.8%.
+// whole number of rounds.  Over 130 random searches and tail searches the choice is on average 1.8%
+// and 1.5% behind the best of 17 counts up to 384.
 //
 // Within a long item the work-groups of an XCD drift apart, the older ones ahead, and no longer
 // read the same spectra out of the caches: about 2% for each doubling past DRIFT templates (128

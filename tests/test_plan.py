@@ -73,7 +73,6 @@ TAIL_PLANS = {
 # the same in plain searches
 SEARCH_PLANS = {
     (200, 10, 1024, 14, 1): {72},
-    (200, 10, 1024, 14, 16): {72},
     (16, 64, 600, 200, 1): {16},
     (96, 3, 512, 40, 1): {24, 32},
     (64, 30, 2000, 40, 256): {64},
