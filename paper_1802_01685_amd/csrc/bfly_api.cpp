@@ -547,7 +547,8 @@ bf_status device_slots(int* slots) {
 // kernels deal each XCD whole ranges when their count is a multiple of 8, so their plan counts one
 // XCD's items on its 64 work-groups: whole rounds of the largest item, whose length in templates
 // has 3 for its set-up, and for each bin's end 1, or 16 where its row is decimated (atomics of 64
-// lanes on one word).  Of plans within 2%, the one of the shortest items: of two work-groups on a CU
+// lanes on one word).  Of plans within 2%, the one of the shortest items (of equally long ones the
+// fewest: 8 blocks against 44 bins of 1 49 us with 24 ranges, 60 with 40): of two work-groups on a CU
 // the older one's waves win the issue slots (2.65 against 3.8 us per template in the search), and
 // long items leave the younger one's last running on alone.  65,536 x 4096 on 31 blocks takes
 // 12.6 ms with 16 ranges, 11.9 with 128 and 11.3 with 256; 720,000 x 2000 on 42 blocks 178 ms with
@@ -575,14 +576,16 @@ int32_t plan_fft_ranges(const BankDev& b, int64_t total_tiles, int slots, const 
   const int64_t conc = 2 * (int64_t)slots, per_xcd = std::max<int64_t>(conc / 8, 1);
   if (b.fft_m == 4096 && b.n_bins >= 8) {
     const int64_t bin = b.n_fdot + (sp.t_block > 1 ? 16 : 1);
+    int64_t best_bins = INT64_MAX;
     for (int32_t r = 8; r <= b.n_bins; r += 8) {
       const int64_t items = total_tiles * r;
       if (items > MAX_FFT_ITEMS) break;
       const int64_t bins = (b.n_bins + r - 1) / r;
       const int64_t rounds = (total_tiles * (r / 8) + per_xcd - 1) / per_xcd;
       const double cost = (double)(rounds * (bins * bin + 3)) * drift(bins * b.n_fdot);
-      if (cost < 1.02 * best_cost) {
+      if (bins < best_bins && cost < 1.02 * best_cost) {
         best_cost = std::min(best_cost, cost);
+        best_bins = bins;
         best_r = r;
       }
       if (items > 64 * conc && bins * b.n_fdot <= DRIFT) break;
